@@ -1324,19 +1324,109 @@ sim_status finish_load(sim_ctx *c, Ranges &R) {
             res.threads = k == 1 ? 1024 : k == 2 ? 512 : 256;
         }
     }
+    // Route engine: round-robin, at most 1024 traffic links, 32 input ports
+    // and 4 lines per cycle and link; a line's remaining route (out-link index
+    // per hop, then its flow if some line waits on others) in 32 bits.
+    struct RouteLayout {
+        bool lds_ok = false, hbm_ok = false;
+        int32_t bits = 1, np = 0, zero = 0;
+        int64_t off[8] = {};
+        int64_t bytes_lds = 0, bytes_hbm = 0;
+    } rt;
+    std::vector<int32_t> rt_lanes, rt_pslot, rt_tin, rt_obase;
+    std::vector<uint32_t> rt_flow_code;
+    if (c->arb == SIM_ARB_ROUND_ROBIN && !credits && nl >= 1 && nl <= 1024 && bm <= 4) {
+        bool ok = true;
+        rt_lanes = fsrc;
+        std::sort(rt_lanes.begin(), rt_lanes.end());  // a node's out-links follow each other
+        std::vector<int32_t> first_out(c->n, 0), n_out(c->n, 0), in_base(c->n, -1), out_idx(m, 0);
+        for (int32_t i = 0; i < nl; i++) {
+            const int32_t l = rt_lanes[i], u = c->tail[l], v = c->col_idx[l];
+            if (n_out[u] == 0) first_out[u] = i;
+            out_idx[l] = n_out[u]++;
+            ok = ok && nports_tail[l] <= 32;
+            for (int32_t w : {u, v})
+                if (in_base[w] < 0) {
+                    in_base[w] = rt.np;
+                    rt.np += nports[w];
+                }
+        }
+        int32_t most = 0;
+        for (int32_t v = 0; v < c->n; v++) most = std::max(most, n_out[v]);
+        while ((1 << rt.bits) - 1 < most) rt.bits++;
+        int32_t fbits = 0;
+        while (any_preds && (int64_t(1) << fbits) < nflows) fbits++;
+        rt_flow_code.assign(nflows, 0u);
+        for (int32_t f = 0; f < nflows && ok; f++) {
+            const int32_t H = flow_hops[f];
+            if ((int64_t)H * rt.bits + fbits > 32) {
+                ok = false;
+                break;
+            }
+            uint64_t w = 0;
+            for (int32_t h = 1; h < H; h++)
+                w |= (uint64_t)out_idx[c->path_link[c->flow_path[f] + h]] << ((h - 1) * rt.bits);
+            w |= (uint64_t)((1u << rt.bits) - 1u) << ((H - 1) * rt.bits);
+            if (any_preds) w |= (uint64_t)(uint32_t)f << (H * rt.bits);
+            rt_flow_code[f] = (uint32_t)w;
+        }
+        for (int32_t i = 0; i < nl; i++) {
+            const int32_t l = rt_lanes[i], u = c->tail[l], v = c->col_idx[l];
+            rt_pslot.push_back(in_base[v] + port_at_head[l]);
+            rt_tin.push_back(in_base[u]);
+            rt_obase.push_back(first_out[v]);
+        }
+        int64_t o2 = 0;
+        auto take = [&](int q, int64_t bytes) {
+            rt.off[q] = o2;
+            o2 = align16(o2 + bytes);
+        };
+        take(0, (int64_t)bm * nl * 4);
+        take(2, (int64_t)rt.np * 4);
+        take(3, bm > 1 ? (int64_t)rt.np * 4 : 0);
+        take(4, any_preds ? (int64_t)nflows * 4 : 0);
+        take(5, 32);
+        rt.zero = (int32_t)std::min<int64_t>(o2 / 4, INT32_MAX);
+        take(1, (int64_t)bm * rt.np * 8);
+        rt.bytes_hbm = o2;
+        take(6, lf * 8);
+        take(7, lf * 4);
+        rt.bytes_lds = o2;
+        rt.hbm_ok = ok && rt.bytes_hbm <= kLds && lf * 16 <= (int64_t)UINT32_MAX;
+        rt.lds_ok = ok && rt.bytes_lds <= kLds;
+    }
     if ((credits && R.whole) || fair) wv.ok = false;
     const bool lane_ok = !credits && !fair && nl >= 1 && nl <= 1024 && bm <= 64 && lay_lds.bytes <= kLds;
     const bool lanehbm_ok = !credits && !fair && nl >= 1 && nl <= 1024 && bm <= 64 && lay_hbm.bytes <= kLds;
     const bool b1_usable = !credits && !fair && nl >= 1 && b1_ok;
     int engine = simgpu::kEngineWorkgroup;
+    // Rings in LDS while every scenario's workgroup is resident at once (16
+    // waves of 128 registers per compute unit), else in device memory, which
+    // holds more workgroups per compute unit (a k = 4 fat-tree sweep, ms per
+    // launch with rings in LDS / device memory: route engine 122 / 138 at 512
+    // scenarios, 18.0 / 16.5 at 1024 and 26.2 / 16.3 at 2048 of a smaller
+    // message; lane engine 34.1 / 22.7 at 512).
+    auto all_resident = [&](int64_t lds) {
+        const int64_t waves = (nl + 63) / 64;
+        return (int64_t)c->S <= wave_blocks * std::min<int64_t>(kLds / std::max<int64_t>(lds, 1), 16 / waves);
+    };
+    // One line per cycle everywhere: the compact engine with one lane per
+    // thread takes half the lane engine's time per cycle (k = 4 to 8
+    // fat-trees under lowest id: 1.1-1.3 against 2.0-3.2 us; a 4 x 2 torus
+    // of one wave: 1.0 against 1.5 us).
+    const bool b1_first = b1_usable && nl <= 1024;
     if (wv.ok) engine = simgpu::kEngineWave;
-    else if (lane_ok) engine = simgpu::kEngineLane;
+    else if (rt.lds_ok && (!rt.hbm_ok || all_resident(rt.bytes_lds))) engine = simgpu::kEngineRoute;
+    else if (rt.hbm_ok) engine = simgpu::kEngineRouteHbm;
+    else if (b1_first) engine = simgpu::kEngineB1;
+    else if (lane_ok && (!lanehbm_ok || all_resident(lay_lds.bytes))) engine = simgpu::kEngineLane;
     else if (b1_usable) engine = simgpu::kEngineB1;
     else if (lanehbm_ok) engine = simgpu::kEngineLaneHbm;
     // One large topology whose lines move one per cycle per link: the grid
     // engine's one-line form spreads it over many CUs at a lower time per
-    // processed cycle than the single-workgroup compact and HBM engines.
-    if (grid_ok && gl.one && (engine == simgpu::kEngineB1 || engine == simgpu::kEngineLaneHbm ||
+    // processed cycle than the single-workgroup compact engine with several
+    // lanes per thread and the HBM lane engine.
+    if (grid_ok && gl.one && ((engine == simgpu::kEngineB1 && !b1_first) || engine == simgpu::kEngineLaneHbm ||
                               engine == simgpu::kEngineWorkgroup))
         engine = simgpu::kEngineGrid;
     if (engine == simgpu::kEngineWorkgroup && res.ok) engine = simgpu::kEngineResident;
@@ -1354,9 +1444,12 @@ sim_status finish_load(sim_ctx *c, Ranges &R) {
         if (!std::strcmp(ev, "wave")) want = simgpu::kEngineWave;
         if (!std::strcmp(ev, "grid")) want = simgpu::kEngineGrid;
         if (!std::strcmp(ev, "resident")) want = simgpu::kEngineResident;
+        if (!std::strcmp(ev, "route")) want = simgpu::kEngineRoute;
+        if (!std::strcmp(ev, "routehbm")) want = simgpu::kEngineRouteHbm;
         const bool ok = want == simgpu::kEngineWorkgroup || (want == simgpu::kEngineWave && wv.ok) ||
                         (want == simgpu::kEngineResident && res.ok) ||
                         (want == simgpu::kEngineGrid && grid_ok) ||
+                        (want == simgpu::kEngineRoute && rt.lds_ok) || (want == simgpu::kEngineRouteHbm && rt.hbm_ok) ||
                         (want == simgpu::kEngineLane && lane_ok) || (want == simgpu::kEngineLaneHbm && lanehbm_ok) ||
                         (want == simgpu::kEngineB1 && b1_usable);
         if (want < 0 || !ok) return fail(c, SIM_ERR_INVALID_ARG, std::string("SIMGPU_ENGINE=") + ev + " is not usable here");
@@ -1366,6 +1459,8 @@ sim_status finish_load(sim_ctx *c, Ranges &R) {
     // Lane order: traffic links ascending; the compact engine puts the links
     // that start a stream first so that stream j is owned by thread j.
     std::vector<int32_t> lane_link(fsrc);
+    const bool route = engine == simgpu::kEngineRoute || engine == simgpu::kEngineRouteHbm;
+    if (route) lane_link = rt_lanes;
     if (engine == simgpu::kEngineB1)
         std::stable_partition(lane_link.begin(), lane_link.end(), [&](int32_t l) { return has_stream[l] != 0; });
     for (int32_t i = 0; i < nl; i++) link_lane[lane_link[i]] = i;
@@ -1410,6 +1505,8 @@ sim_status finish_load(sim_ctx *c, Ranges &R) {
                               : engine == simgpu::kEngineWave ? wv.bytes
                               : engine == simgpu::kEngineGrid ? gl.bytes
                               : engine == simgpu::kEngineResident ? res.bytes
+                              : engine == simgpu::kEngineRoute ? rt.bytes_lds
+                              : engine == simgpu::kEngineRouteHbm ? rt.bytes_hbm
                                                               : lay.bytes;
 
     // everything below touches the device
@@ -1666,6 +1763,20 @@ sim_status finish_load(sim_ctx *c, Ranges &R) {
             UP(gl.tro, gd_tro);
         }
     }
+    if (route) {
+        for (int q = 0; q < 8; q++) d.rt_off[q] = (int32_t)rt.off[q];
+        d.rt_zero = rt.zero;
+        d.rt_np = rt.np;
+        d.rt_bits = rt.bits;
+        std::vector<uint32_t> rt_code(nr);
+        for (int64_t j = 0; j < nr; j++) rt_code[j] = rt_flow_code[rflow[order[j]]];
+        int32_t *tmp_rt_pslot, *tmp_rt_tin, *tmp_rt_obase;
+        uint32_t *tmp_rt_code;
+        UP(rt_pslot, rt_pslot);
+        UP(rt_tin, rt_tin);
+        UP(rt_obase, rt_obase);
+        UP(rt_code, rt_code);
+    }
     if (engine == simgpu::kEngineWave) {
         uint32_t *tmp_wv_lfb, *tmp_wv_lfx, *tmp_wv_duo;
         if (wv_duo.empty()) wv_duo.push_back(0);
@@ -1689,7 +1800,8 @@ sim_status finish_load(sim_ctx *c, Ranges &R) {
     sl = StateLayout{};
     sl.add(&DevNet::status, S);
     sl.add(&DevNet::cycles, S);
-    if (engine == simgpu::kEngineLaneHbm || engine == simgpu::kEngineGrid) sl.add(&DevNet::gfifo, S * (size_t)lf);
+    if (engine == simgpu::kEngineLaneHbm || engine == simgpu::kEngineGrid || engine == simgpu::kEngineRouteHbm)
+        sl.add(&DevNet::gfifo, S * (size_t)lf);
     if (engine == simgpu::kEngineGrid) {
         sl.add(&DevNet::gd_pub, 4 * (size_t)nl);
         if (gl.one) sl.add(&DevNet::gd_tpub, 4 * (size_t)nl);

@@ -188,6 +188,17 @@ struct DevNet {
     const int32_t *gd_iptr, *gd_inl;  // [gd_nb+1] CSR: per node of the workgroup, for each input
                                       //   port the local source side feeding it (-1: stream or none)
 
+    // route engine (round-robin, thread i owns traffic link i): LDS byte
+    // offsets (request words, posts, grants, voids, delivered counters,
+    // reduction slots, rings, their ready cycles), the 32-bit words to clear
+    // at the start of LDS, post slots, bits per hop of a route word
+    int32_t rt_off[8];
+    int32_t rt_zero, rt_np, rt_bits;
+    const int32_t *rt_pslot;  // [nl] post slot of a lane's FIFO: its port at the node it leads to
+    const int32_t *rt_tin;    // [nl] first post slot of the node a lane starts at
+    const int32_t *rt_obase;  // [nl] first lane that starts at the node a lane leads to
+    const uint32_t *rt_code;  // [nr] route word of a range's lines on their first link
+
     // resident workgroup engine: per-link state, link parameters and the
     // cycle's request records of a scenario in LDS (byte offsets wr_off),
     // records past wr_rcap in a per-scenario HBM overflow area of wr_ovf
@@ -214,7 +225,7 @@ struct DevNet {
 };
 
 enum : int32_t { kEngineWorkgroup = 0, kEngineLane = 1, kEngineLaneHbm = 2, kEngineB1 = 3, kEngineWave = 4,
-                 kEngineGrid = 5, kEngineResident = 6 };
+                 kEngineGrid = 5, kEngineResident = 6, kEngineRoute = 7, kEngineRouteHbm = 8 };
 // Wave engine entry words: line id << kWaveXShift | local-flow index (0..3)
 // << 5, the low five bits free for a request slot number (so line ids must
 // be below 2^25 - 1).
@@ -245,5 +256,6 @@ hipError_t launch_b1_any(const DevNet &d, hipStream_t st);
 hipError_t launch_wave_any(const DevNet &d, hipStream_t st);
 hipError_t launch_grid_any(const DevNet &d, hipStream_t st);
 hipError_t launch_resident(const DevNet &d, hipStream_t st);
+hipError_t launch_route(const DevNet &d, hipStream_t st);
 
 }  // namespace simgpu
