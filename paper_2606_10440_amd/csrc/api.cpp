@@ -457,6 +457,9 @@ struct GridLayout {
     // windowed form
     int32_t window = 0, sring_max = 0, cring_max = 0;
     std::vector<int32_t> sro, tro;
+    // windowed form, one wavefront per workgroup
+    bool wave = false;
+    std::vector<int32_t> pslot, tbase;
 };
 
 GridLayout grid_layout(const sim_ctx *c, const std::vector<int32_t> &fsrc, const std::vector<char> &has_stream,
@@ -581,6 +584,18 @@ GridLayout grid_layout(const sim_ctx *c, const std::vector<int32_t> &fsrc, const
             }
             g.iptr.push_back((int32_t)g.inl.size());
             g.inl_max = std::max(g.inl_max, (int32_t)(g.inl.size() - base));
+        }
+        // post slot of every lane's FIFO and first target side at its head
+        // node (0 where that node sends nothing on)
+        std::vector<int32_t> first_t(c->n, 0);
+        for (int32_t i = nl - 1; i >= 0; i--) first_t[c->tail[fsrc[i]]] = g.tloc[i];
+        g.pslot.assign(nl, 0);
+        g.tbase.assign(nl, 0);
+        for (int32_t i = 0; i < nl; i++) {
+            const int32_t v = c->col_idx[fsrc[i]];
+            if (node_off[v] < 0) continue;
+            g.pslot[i] = node_off[v] + port_at_head[fsrc[i]];
+            g.tbase[i] = first_t[v];
         }
         if (g.inl.empty()) g.inl.push_back(-1);
         int64_t b1 = a16(8 * NT * (c->arb == SIM_ARB_LOWEST_ID ? 2 : 1));
@@ -1188,6 +1203,89 @@ sim_status finish_load(sim_ctx *c, Ranges &R) {
     // engine (both forms)
     const bool credits = !c->credit.empty();
     const bool fair = (c->arb & SIM_ARB_FAIR_CLASSES) != 0;
+    // Route engine: round-robin, at most 1024 traffic links, 32 input ports
+    // and 4 lines per cycle and link; a line's remaining route (out-link index
+    // per hop, then its flow if some line waits on others) in 32 bits.
+    struct RouteLayout {
+        bool lds_ok = false, hbm_ok = false;
+        int32_t bits = 1, np = 0, zero = 0;
+        int64_t off[8] = {};
+        int64_t bytes_lds = 0, bytes_hbm = 0;
+    } rt;
+    std::vector<int32_t> rt_lanes, rt_pslot, rt_tin, rt_obase;
+    std::vector<uint32_t> rt_flow_code;
+    const bool rt_try = c->arb == SIM_ARB_ROUND_ROBIN && !credits && nl >= 1 && nl <= 1024 && bm <= 4;
+    const bool win_try = credits && c->S == 1 && !fair && nl >= 1 && bmax == 1 && !any_preds;
+    bool code_ok = rt_try || win_try;
+    std::vector<int32_t> first_out, n_out, out_idx;
+    if (code_ok) {
+        rt_lanes = fsrc;
+        std::sort(rt_lanes.begin(), rt_lanes.end());  // a node's out-links follow each other
+        first_out.assign(c->n, 0);
+        n_out.assign(c->n, 0);
+        out_idx.assign(m, 0);
+        for (int32_t i = 0; i < nl; i++) {
+            const int32_t l = rt_lanes[i], u = c->tail[l];
+            if (n_out[u] == 0) first_out[u] = i;
+            out_idx[l] = n_out[u]++;
+        }
+        int32_t most = 0;
+        for (int32_t v = 0; v < c->n; v++) most = std::max(most, n_out[v]);
+        while ((int64_t(1) << rt.bits) - 1 < most) rt.bits++;
+        int32_t fbits = 0;
+        while (any_preds && (int64_t(1) << fbits) < nflows) fbits++;
+        rt_flow_code.assign(nflows, 0u);
+        for (int32_t f = 0; f < nflows; f++) {
+            const int32_t H = flow_hops[f];
+            if ((int64_t)H * rt.bits + fbits > 32) {
+                code_ok = false;
+                break;
+            }
+            uint64_t w = 0;
+            for (int32_t h = 1; h < H; h++)
+                w |= (uint64_t)out_idx[c->path_link[c->flow_path[f] + h]] << ((h - 1) * rt.bits);
+            w |= (uint64_t)((1u << rt.bits) - 1u) << ((H - 1) * rt.bits);
+            if (any_preds) w |= (uint64_t)(uint32_t)f << (H * rt.bits);
+            rt_flow_code[f] = (uint32_t)w;
+        }
+    }
+    if (rt_try && code_ok) {
+        bool ok = true;
+        std::vector<int32_t> in_base(c->n, -1);
+        for (int32_t i = 0; i < nl; i++) {
+            const int32_t l = rt_lanes[i];
+            ok = ok && nports_tail[l] <= 32;
+            for (int32_t w : {c->tail[l], c->col_idx[l]})
+                if (in_base[w] < 0) {
+                    in_base[w] = rt.np;
+                    rt.np += nports[w];
+                }
+        }
+        for (int32_t i = 0; i < nl; i++) {
+            const int32_t l = rt_lanes[i], u = c->tail[l], v = c->col_idx[l];
+            rt_pslot.push_back(in_base[v] + port_at_head[l]);
+            rt_tin.push_back(in_base[u]);
+            rt_obase.push_back(first_out[v]);
+        }
+        int64_t o2 = 0;
+        auto take = [&](int q, int64_t bytes) {
+            rt.off[q] = o2;
+            o2 = align16(o2 + bytes);
+        };
+        take(0, (int64_t)bm * nl * 4);
+        take(2, (int64_t)rt.np * 4);
+        take(3, bm > 1 ? (int64_t)rt.np * 4 : 0);
+        take(4, any_preds ? (int64_t)nflows * 4 : 0);
+        take(5, 32);
+        rt.zero = (int32_t)std::min<int64_t>(o2 / 4, INT32_MAX);
+        take(1, (int64_t)bm * rt.np * 8);
+        rt.bytes_hbm = o2;
+        take(6, lf * 8);
+        take(7, lf * 4);
+        rt.bytes_lds = o2;
+        rt.hbm_ok = ok && rt.bytes_hbm <= kLds && lf * 16 <= (int64_t)UINT32_MAX;
+        rt.lds_ok = ok && rt.bytes_lds <= kLds;
+    }
     // Grid engine (one scenario over many workgroups): nodes are split over
     // the workgroups by longest-processing-time assignment of their lanes
     // (target sides of out-links, source sides of in-links, a stream), so
@@ -1195,22 +1293,39 @@ sim_status finish_load(sim_ctx *c, Ranges &R) {
     GridLayout gl;
     const bool grid_try = c->S == 1 && !fair && nl >= 1 && bm <= 64;
     if (grid_try) {
-        int want_nb = 32;
-        if (const char *ev = std::getenv("SIMGPU_GRID_WGS")) want_nb = std::max(1, std::min(32, std::atoi(ev)));
-        gl = grid_layout(c, fsrc, has_stream, feeders, fsrc_pos, bmax, bm, nflows, pd_flow, want_nb, port_at_head,
-                         nports);
+        // With credit delays a window of win cycles runs between exchanges: a
+        // workgroup's cycles shrink with its nodes, so windows that pay for an
+        // exchange over all dies take one workgroup per compute unit, shorter
+        // ones and graphs of about 32 nodes one die's (k = 8 fat-tree, 208
+        // nodes, ms with 32 / 256 workgroups: 12.4 / 15.1 at windows of 2
+        // cycles, 6.3 / 5.3 at 8, 10.7 / 8.2 at 32, 15.9 / 11.4 at 64; k = 4,
+        // 36 nodes: 2.43 / 2.55 at 64).
+        int32_t win = 0;
+        if (credits) {
+            win = INT32_MAX;
+            for (int32_t l : fsrc) win = std::min(win, std::min(c->lat[l], c->credit[l]));
+        }
+        const int few_nb = 32;
+        int want_nb = win_try && code_ok && win >= 8 && c->n >= 64 ? wave_blocks : few_nb;
+        if (const char *ev = std::getenv("SIMGPU_GRID_WGS")) want_nb = std::max(1, std::min(wave_blocks, std::atoi(ev)));
+        auto layout = [&](int nb) {
+            gl = grid_layout(c, fsrc, has_stream, feeders, fsrc_pos, bmax, bm, nflows, pd_flow, nb, port_at_head,
+                             nports);
+        };
+        layout(want_nb);
+        gl.wave = win_try && code_ok && gl.one && win >= 2 && gl.ns_max <= 64 && gl.nt_max <= 64 &&
+                  !std::getenv("SIMGPU_GRID_GENERAL");
+        if (!gl.wave && want_nb > few_nb) layout(few_nb);  // the other forms run on one die
         if (std::getenv("SIMGPU_GRID_GENERAL")) gl.one = false;  // tests: the general form on b = 1 graphs
         if (gl.one && gl.one_bytes <= kLds) {
             gl.bytes = gl.one_bytes;
             gl.threads = gl.one_threads;
         } else {
-            gl.one = false;
+            gl.one = gl.wave = false;
         }
         // Credit delays: the windowed form, when every traffic link has
         // latency and credit delay of at least 2 and no line waits on another.
         if (credits) {
-            int32_t win = INT32_MAX;
-            for (int32_t l : fsrc) win = std::min(win, std::min(c->lat[l], c->credit[l]));
             if (gl.one && !any_preds && win >= 2) {
                 std::vector<int32_t> ring_of(nl);
                 for (int32_t i = 0; i < nl; i++) ring_of[i] = fifo_mask[fsrc[i]] + 1;
@@ -1234,6 +1349,11 @@ sim_status finish_load(sim_ctx *c, Ranges &R) {
                 int64_t b = a16(8 * (int64_t)gl.nt_max * (c->arb == SIM_ARB_LOWEST_ID ? 2 : 1));
                 if (c->arb == SIM_ARB_ROUND_ROBIN) b += a16(8 * (int64_t)gl.ns_max) + a16(4 * (int64_t)gl.inl_max);
                 b += a16(16 * smax) + a16(4 * tmax) + a16(4 * 4 * 2 * 16) + a16(4 * 32);
+                if (gl.wave) {
+                    b = a16(8 * (int64_t)gl.nt_max) + a16(8 * (int64_t)gl.inl_max) + a16(4 * (int64_t)gl.inl_max) +
+                        a16(16 * smax) + a16(4 * tmax);
+                    gl.threads = 64;
+                }
                 gl.window = win;
                 gl.sring_max = (int32_t)smax;
                 gl.cring_max = (int32_t)tmax;
@@ -1323,77 +1443,6 @@ sim_status finish_load(sim_ctx *c, Ranges &R) {
             res.bytes = o + rb * res.rcap;
             res.threads = k == 1 ? 1024 : k == 2 ? 512 : 256;
         }
-    }
-    // Route engine: round-robin, at most 1024 traffic links, 32 input ports
-    // and 4 lines per cycle and link; a line's remaining route (out-link index
-    // per hop, then its flow if some line waits on others) in 32 bits.
-    struct RouteLayout {
-        bool lds_ok = false, hbm_ok = false;
-        int32_t bits = 1, np = 0, zero = 0;
-        int64_t off[8] = {};
-        int64_t bytes_lds = 0, bytes_hbm = 0;
-    } rt;
-    std::vector<int32_t> rt_lanes, rt_pslot, rt_tin, rt_obase;
-    std::vector<uint32_t> rt_flow_code;
-    if (c->arb == SIM_ARB_ROUND_ROBIN && !credits && nl >= 1 && nl <= 1024 && bm <= 4) {
-        bool ok = true;
-        rt_lanes = fsrc;
-        std::sort(rt_lanes.begin(), rt_lanes.end());  // a node's out-links follow each other
-        std::vector<int32_t> first_out(c->n, 0), n_out(c->n, 0), in_base(c->n, -1), out_idx(m, 0);
-        for (int32_t i = 0; i < nl; i++) {
-            const int32_t l = rt_lanes[i], u = c->tail[l], v = c->col_idx[l];
-            if (n_out[u] == 0) first_out[u] = i;
-            out_idx[l] = n_out[u]++;
-            ok = ok && nports_tail[l] <= 32;
-            for (int32_t w : {u, v})
-                if (in_base[w] < 0) {
-                    in_base[w] = rt.np;
-                    rt.np += nports[w];
-                }
-        }
-        int32_t most = 0;
-        for (int32_t v = 0; v < c->n; v++) most = std::max(most, n_out[v]);
-        while ((1 << rt.bits) - 1 < most) rt.bits++;
-        int32_t fbits = 0;
-        while (any_preds && (int64_t(1) << fbits) < nflows) fbits++;
-        rt_flow_code.assign(nflows, 0u);
-        for (int32_t f = 0; f < nflows && ok; f++) {
-            const int32_t H = flow_hops[f];
-            if ((int64_t)H * rt.bits + fbits > 32) {
-                ok = false;
-                break;
-            }
-            uint64_t w = 0;
-            for (int32_t h = 1; h < H; h++)
-                w |= (uint64_t)out_idx[c->path_link[c->flow_path[f] + h]] << ((h - 1) * rt.bits);
-            w |= (uint64_t)((1u << rt.bits) - 1u) << ((H - 1) * rt.bits);
-            if (any_preds) w |= (uint64_t)(uint32_t)f << (H * rt.bits);
-            rt_flow_code[f] = (uint32_t)w;
-        }
-        for (int32_t i = 0; i < nl; i++) {
-            const int32_t l = rt_lanes[i], u = c->tail[l], v = c->col_idx[l];
-            rt_pslot.push_back(in_base[v] + port_at_head[l]);
-            rt_tin.push_back(in_base[u]);
-            rt_obase.push_back(first_out[v]);
-        }
-        int64_t o2 = 0;
-        auto take = [&](int q, int64_t bytes) {
-            rt.off[q] = o2;
-            o2 = align16(o2 + bytes);
-        };
-        take(0, (int64_t)bm * nl * 4);
-        take(2, (int64_t)rt.np * 4);
-        take(3, bm > 1 ? (int64_t)rt.np * 4 : 0);
-        take(4, any_preds ? (int64_t)nflows * 4 : 0);
-        take(5, 32);
-        rt.zero = (int32_t)std::min<int64_t>(o2 / 4, INT32_MAX);
-        take(1, (int64_t)bm * rt.np * 8);
-        rt.bytes_hbm = o2;
-        take(6, lf * 8);
-        take(7, lf * 4);
-        rt.bytes_lds = o2;
-        rt.hbm_ok = ok && rt.bytes_hbm <= kLds && lf * 16 <= (int64_t)UINT32_MAX;
-        rt.lds_ok = ok && rt.bytes_lds <= kLds;
     }
     if ((credits && R.whole) || fair) wv.ok = false;
     const bool lane_ok = !credits && !fair && nl >= 1 && nl <= 1024 && bm <= 64 && lay_lds.bytes <= kLds;
@@ -1725,7 +1774,7 @@ sim_status finish_load(sim_ctx *c, Ranges &R) {
             gpath[q] = v >= 0 ? gl.tloc[v] : -1 - (gl.floc[-v - 1] >= 0 ? gl.floc[-v - 1] : gl.fl_max);
         }
         d.gd_nb = gl.nb;
-        d.gd_stride = 8;  // blocks w * 8: one die's CUs when blocks go round-robin over the 8 dies
+        d.gd_stride = gl.nb > 32 ? 1 : 8;  // blocks w * 8: one die's CUs when blocks go round-robin over the 8 dies
         if (const char *ev = std::getenv("SIMGPU_GRID_STRIDE")) {  // tests: workgroups spread over the dies
             const int v = std::atoi(ev);
             if (v >= 1 && v <= 8) d.gd_stride = v;
@@ -1757,25 +1806,33 @@ sim_status finish_load(sim_ctx *c, Ranges &R) {
             UP(gl.iptr, gd_iptr);
             UP(gl.inl, gd_inl);
         }
+        d.gd_wave = gl.wave ? 1 : 0;
+        if (gl.wave) {
+            int32_t *tmp_gd_pslot, *tmp_gd_tbase;
+            UP(gl.pslot, gd_pslot);
+            UP(gl.tbase, gd_tbase);
+        }
         if (gl.window > 0) {
             int32_t *tmp_gd_sro, *tmp_gd_tro;
             UP(gl.sro, gd_sro);
             UP(gl.tro, gd_tro);
         }
     }
+    if (route || (engine == simgpu::kEngineGrid && gl.wave)) {
+        d.rt_bits = rt.bits;
+        std::vector<uint32_t> rt_code(nr);
+        for (int64_t j = 0; j < nr; j++) rt_code[j] = rt_flow_code[rflow[order[j]]];
+        uint32_t *tmp_rt_code;
+        UP(rt_code, rt_code);
+    }
     if (route) {
         for (int q = 0; q < 8; q++) d.rt_off[q] = (int32_t)rt.off[q];
         d.rt_zero = rt.zero;
         d.rt_np = rt.np;
-        d.rt_bits = rt.bits;
-        std::vector<uint32_t> rt_code(nr);
-        for (int64_t j = 0; j < nr; j++) rt_code[j] = rt_flow_code[rflow[order[j]]];
         int32_t *tmp_rt_pslot, *tmp_rt_tin, *tmp_rt_obase;
-        uint32_t *tmp_rt_code;
         UP(rt_pslot, rt_pslot);
         UP(rt_tin, rt_tin);
         UP(rt_obase, rt_obase);
-        UP(rt_code, rt_code);
     }
     if (engine == simgpu::kEngineWave) {
         uint32_t *tmp_wv_lfb, *tmp_wv_lfx, *tmp_wv_duo;

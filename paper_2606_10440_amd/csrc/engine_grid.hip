@@ -38,6 +38,8 @@
 // holds at least cap entries and the writer respects cap).
 #include <hip/hip_runtime.h>
 
+#include <type_traits>
+
 #include "engine_common.h"
 
 namespace simgpu {
@@ -1539,6 +1541,363 @@ __global__ void __launch_bounds__(1024) engine_gridw(DevNet d) {
     }
 }
 
+// ----------------------------------------------------------------------------
+// Windowed form, one wavefront per workgroup: the same windows and exchange,
+// for workgroups of at most 64 source and 64 target sides whose lines carry
+// their remaining route in one word (gd_code; the route engine's form).
+// Nothing in a window needs a barrier: LDS operations of one wave complete in
+// issue order, so its phases are separated by compiler barriers only, and
+// the nodes are spread over up to one workgroup per compute unit, because a
+// workgroup's cycles shrink with its nodes while the exchange is paid once
+// per window.  A cycle is followed by the earliest one in which some request
+// of the workgroup can change something: a head that becomes ready, or, at a
+// target that turned requests away, t + 1 or (full) its next credit return.
+// Entries and departure cycles are device-scope stores, complete before the
+// counts that cover them, so that no cache write-back is needed; the new
+// entries of up to eight sides are read together, one entry per lane.
+// Measured on a k = 8 fat-tree all-to-all of 64 lines per pair (window 100
+// cycles), per launch: 385 ms in the multi-wave form on 32 workgroups, 169 on
+// 32 one-wave workgroups, 125 on 208.  A cycle takes 0.62 us (about 265
+// instructions and three LDS round trips of one wave); of the 39 us per
+// window at 208 workgroups, 4 are the exchange, the rest the cycles of the
+// slowest workgroup of each window.
+template <int ARB>
+__global__ void __launch_bounds__(64) engine_gridv(DevNet d) {
+    extern __shared__ __align__(16) unsigned char smem[];
+    if (blockIdx.x % (unsigned)d.gd_stride) return;
+    const int w = (int)(blockIdx.x / (unsigned)d.gd_stride);
+    if (w >= d.gd_nb) return;
+    const int j = threadIdx.x;
+    const int nl = d.nl, m = d.m, NB = d.gd_nb;
+    const int sb = d.gd_sptr[w], ns = d.gd_sptr[w + 1] - sb;
+    const int tb = d.gd_tptr[w], nt = d.gd_tptr[w + 1] - tb;
+    const bool hs = j < ns, ht = j < nt;
+    const uint32_t W = (uint32_t)d.gd_window;
+    const uint32_t rbits = (uint32_t)d.rt_bits, rsink = (1u << rbits) - 1u;
+    constexpr unsigned long long kNone = ARB == 0 ? ~0ull : 0ull;
+    constexpr uint32_t kOwn = 0xFFFFFFFFu;  // ARB == 0: the stream's "slot" in a request word
+
+    size_t off = 0;
+    auto carve = [&](size_t bytes) {
+        unsigned char *p = smem + off;
+        off = (off + bytes + 15) & ~(size_t)15;
+        return p;
+    };
+    unsigned long long *word = (unsigned long long *)carve(8 * (size_t)d.gd_nt_max);  // requests of a target
+    uint2 *post = (uint2 *)carve(8 * (size_t)d.gd_inl_max);      // per input port: {line, route from the target on}
+    uint32_t *gr = (uint32_t *)carve(4 * (size_t)d.gd_inl_max);  // per input port: tag of the cycle it was granted in
+    uint4 *sring = (uint4 *)carve(16 * (size_t)d.gd_sring_max);  // {line, route, ready, -} of known entries
+    uint32_t *cring = (uint32_t *)carve(4 * (size_t)d.gd_cring_max);  // cycles popped entries left at
+    auto cbar = []() { __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront"); };
+    // minimum over the wave (every lane active)
+    auto wave_min = [](uint32_t v) -> uint32_t {
+        auto step = [&](auto ctrl) {
+            const uint32_t u = (uint32_t)__builtin_amdgcn_update_dpp((int)kNever, (int)v, decltype(ctrl)::value, 0xF, 0xF, false);
+            v = u < v ? u : v;
+        };
+        step(std::integral_constant<int, 0x111>{});  // row_shr:1, 2, 4, 8
+        step(std::integral_constant<int, 0x112>{});
+        step(std::integral_constant<int, 0x114>{});
+        step(std::integral_constant<int, 0x118>{});
+        step(std::integral_constant<int, 0x142>{});  // row_bcast:15, 31
+        step(std::integral_constant<int, 0x143>{});
+        return (uint32_t)__builtin_amdgcn_readlane((int)v, 63);
+    };
+
+    uint32_t *ring = reinterpret_cast<uint32_t *>(d.gfifo);  // {line, route, ready, cycle it left}
+    uint32_t *comp = d.completion;
+    unsigned long long *tpub = d.gd_tpub;
+    for (int q = j; q < d.gd_nt_max; q += 64) word[q] = kNone;
+    for (int q = j; q < d.gd_inl_max; q += 64) gr[q] = 0u;
+    if (w == 0)
+        for (int q = j; q < m; q += 64)
+            if (d.link_lane[q] < 0) {
+                d.tx_lines[q] = 0;
+                d.busy[q] = 0;
+            }
+
+    // source side
+    uint32_t s_lane = 0, s_fb = 0, s_fm = 0, s_D = 1, s_lo = 0, s_slot = 0, s_tb = 0;
+    unsigned long long s_bit = 0;
+    uint32_t head = 0, tkn = 0;
+    if (hs) {
+        s_lane = (uint32_t)d.gd_slane[sb + j];
+        s_fb = (uint32_t)d.ln_fifo[s_lane];
+        s_fm = (uint32_t)d.ln_mask[s_lane];
+        s_D = (uint32_t)d.credit[d.ln_link[s_lane]];
+        s_bit = 1ull << d.ln_port[s_lane];
+        s_lo = (uint32_t)d.gd_sro[s_lane];
+        s_slot = (uint32_t)d.gd_pslot[s_lane];
+        s_tb = (uint32_t)d.gd_tbase[s_lane];
+    }
+    // target side
+    uint32_t t_lane = 0, t_link = 0, t_L = 0, t_cap = 0, t_P = 1, t_fb = 0, t_fm = 0, t_toff = 0, t_D = 1, t_co = 0;
+    uint32_t tail = 0, ret = 0, pk = 0, rr = 0;  // appended, credits back, pops known
+    uint32_t cr = kNever;                        // when the oldest known owed credit comes back
+    unsigned long long tx = 0;
+    int R = 0, rend = 0;
+    uint32_t o = 0, r_st = 0, r_len = 0, r_code = 0;
+    if (ht) {
+        t_lane = (uint32_t)d.gd_tlane[tb + j];
+        t_link = (uint32_t)d.ln_link[t_lane];
+        t_L = (uint32_t)d.lat[t_link];
+        t_cap = (uint32_t)d.cap[t_link];
+        t_P = (uint32_t)d.ln_P[t_lane];
+        t_fb = (uint32_t)d.ln_fifo[t_lane];
+        t_fm = (uint32_t)d.ln_mask[t_lane];
+        t_D = (uint32_t)d.credit[t_link];
+        t_toff = (uint32_t)d.gd_toff[t_lane];
+        t_co = (uint32_t)d.gd_tro[t_lane];
+        R = d.ln_srbeg[t_lane];
+        rend = d.ln_srend[t_lane];
+        if (R < rend) {
+            r_st = d.r_start[R];
+            r_len = d.r_len[R];
+            r_code = d.rt_code[R];
+        }
+    }
+    cbar();
+
+    uint32_t T0 = 0, maxcomp = 0, tag = 0, done = 0;
+    uint64_t widx = 0, local_cycles = 0;
+    int32_t state = d.T > 0 ? kRunRunning : kRunOk;
+    uint4 he = make_uint4(0, 0, 0, 0);  // head entry (head != tkn)
+
+    while (state == kRunRunning) {
+        const uint32_t wend = T0 + W;  // this window: cycles T0 .. wend - 1
+        uint32_t t = T0;
+        uint32_t offer = kNever;       // this lane's events at or after wend
+        bool over = false;
+        uint32_t out = 0;              // lines completed in this window
+        he = sring[s_lo + (head & s_fm)];
+        cr = ret != pk ? cring[t_co + (ret & t_fm)] + t_D : kNever;
+        for (;;) {
+            tag++;
+            // -------------------------------------------------------- requests
+            const bool rdy = hs & (head != tkn) & (he.z <= t);
+            const uint32_t h = he.y & rsink;
+            const bool snk = rdy & (h == rsink), rq = rdy & (h != rsink);
+            if (rq) {
+                post[s_slot] = make_uint2(he.x, he.y >> rbits);
+                if (ARB == 1) atomicOr(&word[s_tb + h], s_bit);
+                else atomicMin(&word[s_tb + h], ((unsigned long long)he.x << 32) | s_slot);
+            }
+            const uint4 h1 = sring[s_lo + ((head + 1u) & s_fm)];
+            cbar();
+            // -------------------------------------------------------- grants and appends
+            uint32_t tev = kNever;
+            if (ht) {
+                unsigned long long wv = word[j];
+                const bool sr = R < rend;
+                if ((wv != kNone) | sr) {
+                    if (wv != kNone) word[j] = kNone;
+                    if (ARB == 1) {
+                        wv |= sr ? 1ull << (t_P - 1u) : 0ull;
+                    } else if (sr) {
+                        const unsigned long long k = ((unsigned long long)(r_st + o) << 32) | kOwn;
+                        wv = k < wv ? k : wv;
+                    }
+                    while (cr <= t) {  // credits back by t
+                        ret++;
+                        cr = ret != pk ? cring[t_co + (ret & t_fm)] + t_D : kNever;
+                    }
+                    bool more = true;  // a request is left over
+                    if (tail - ret < t_cap) {
+                        bool own;
+                        uint32_t slot;
+                        if (ARB == 1) {
+                            const unsigned long long hi = wv >> rr;
+                            const uint32_t p = hi ? rr + (uint32_t)__builtin_ctzll(hi) : (uint32_t)__builtin_ctzll(wv);
+                            own = sr & (p == t_P - 1u);
+                            slot = t_toff + p;
+                            more = (wv & ~(1ull << p)) != 0ull;
+                            rr = p + 1u == t_P ? 0u : p + 1u;
+                        } else {
+                            slot = (uint32_t)wv;
+                            own = slot == kOwn;
+                        }
+                        uint2 v = make_uint2(r_st + o, r_code);
+                        if (!own) {
+                            v = post[slot];
+                            gr[slot] = tag;
+                        }
+                        unsigned long long *e = reinterpret_cast<unsigned long long *>(ring + 4 * (size_t)(t_fb + (tail & t_fm)));
+                        st_dev(e, (unsigned long long)v.y << 32 | v.x);
+                        st_dev(reinterpret_cast<uint32_t *>(e + 1), t + t_L);
+                        tail++;
+                        tx++;
+                        offer = min(offer, t + t_L);  // its consumer's event
+                        if (own) {
+                            if (++o == r_len) {
+                                o = 0;
+                                R++;
+                                if (R < rend) {
+                                    r_st = d.r_start[R];
+                                    r_len = d.r_len[R];
+                                    r_code = d.rt_code[R];
+                                    // drained here (rare), so that no other
+                                    // cycle waits for its stores
+                                    __builtin_amdgcn_s_waitcnt(0x0F70);
+                                }
+                            }
+                            more = more | (R < rend);
+                        }
+                    }
+                    if (more) tev = tail - ret < t_cap ? t + 1u : max(cr, t + 1u);
+                }
+            }
+            cbar();
+            // -------------------------------------------------------- departures
+            bool gone = snk;
+            if (rq) gone = gr[s_slot] == tag;
+            if (snk) {
+                comp[he.x] = t + 1u;
+                maxcomp = t + 1u;
+            }
+            if (gone) {
+                st_dev(ring + 4 * (size_t)(s_fb + (head & s_fm)) + 3, t);  // the cycle it left
+                head++;
+                offer = min(offer, t + s_D);  // its credit comes back
+                he = h1;
+            }
+            // -------------------------------------------------------- next cycle
+            out += (uint32_t)__builtin_popcountll(__ballot(snk));
+            uint32_t sev = max(he.z, t + 1u);
+            sev = (hs & (head != tkn) & (gone | !rq)) ? sev : kNever;  // (a refused head waits for its target's event)
+            const uint32_t ev = min(sev, tev);
+            local_cycles++;
+            const uint32_t nx = __ballot(ev == t + 1u) != 0ull ? t + 1u : wave_min(ev);
+            if (nx >= wend) {
+                offer = min(offer, ev);
+                break;
+            }
+            if ((uint64_t)nx > d.max_cycles) {
+                over = true;
+                break;
+            }
+            t = nx;
+        }
+        // ------------------------------------------------ exchange
+        const unsigned long long tagw = (unsigned long long)(uint32_t)widx;
+        const int par = (int)(widx & 1u);
+        __builtin_amdgcn_s_waitcnt(0x0F70);  // the window's stores are complete
+        if (hs) st_dev(&tpub[((size_t)par * 2 + 1) * nl + s_lane], (tagw << 32) | head);
+        if (ht) st_dev(&tpub[((size_t)par * 2) * nl + t_lane], (tagw << 32) | tail);
+        const int r3 = (int)(widx % 3u);
+        unsigned long long *wordg = reinterpret_cast<unsigned long long *>(d.gd_sync) + r3;
+        uint32_t *nxtw = d.gd_sync + 6 + r3, *outw = d.gd_sync + 9 + r3;
+        const uint32_t best = wave_min(offer);
+        if (j == 0) {
+            if (best != kNever) __hip_atomic_fetch_min(nxtw, best, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            if (out) __hip_atomic_fetch_add(outw, out, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            __builtin_amdgcn_s_waitcnt(0x0F70);
+            __hip_atomic_fetch_add(wordg, 1ull | (over ? 1ull << 32 : 0ull), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        }
+        // the counts of this window
+        uint32_t ntail = tkn, npk = pk;
+        uint32_t spins = 0;
+        bool stuck = false;
+        for (;;) {
+            bool wait = false;
+            if (hs) {
+                const unsigned long long v = ld_dev(&tpub[((size_t)par * 2) * nl + s_lane]);
+                wait = (v >> 32) != tagw;
+                ntail = (uint32_t)v;
+            }
+            if (ht) {
+                const unsigned long long v = ld_dev(&tpub[((size_t)par * 2 + 1) * nl + t_lane]);
+                wait = wait | ((v >> 32) != tagw);
+                npk = (uint32_t)v;
+            }
+            if (__ballot(wait) == 0ull) break;
+            if (++spins > kSpinLimit) {
+                stuck = true;
+                break;
+            }
+        }
+        // the new entries, and the cycles the newly popped entries left at,
+        // of eight source and eight target sides at a time
+        if (!stuck) {
+            const uint32_t ncs = hs ? ntail - tkn : 0u, nct = ht ? npk - pk : 0u;
+            const int most = ns > nt ? ns : nt;
+            auto lane_of = [](uint32_t v, int q) { return (uint32_t)__builtin_amdgcn_readlane((int)v, q); };
+            for (int g0 = 0; g0 < most; g0 += 8) {
+                uint32_t cmax = 0;
+#pragma unroll
+                for (int u = 0; u < 8; u++)  // (sides past the last count nothing: lanes 0..63 all hold a value)
+                    cmax = max(cmax, max(lane_of(ncs, (g0 + u) & 63), lane_of(nct, (g0 + u) & 63)));
+                for (uint32_t q0 = 0; q0 < cmax; q0 += 64) {
+                    const uint32_t q = q0 + (uint32_t)j;
+                    unsigned long long ex[8];
+                    uint32_t er[8], dc[8];
+#pragma unroll
+                    for (int u = 0; u < 8; u++) {
+                        const int z = (g0 + u) & 63;
+                        if (q < lane_of(ncs, z)) {
+                            const size_t at = (size_t)(lane_of(s_fb, z) + ((lane_of(tkn, z) + q) & lane_of(s_fm, z)));
+                            unsigned long long *e = reinterpret_cast<unsigned long long *>(ring + 4 * at);
+                            ex[u] = ld_dev(e);
+                            er[u] = ld_dev(reinterpret_cast<uint32_t *>(e + 1));
+                        }
+                        if (q < lane_of(nct, z))
+                            dc[u] = ld_dev(ring + 4 * (size_t)(lane_of(t_fb, z) + ((lane_of(pk, z) + q) & lane_of(t_fm, z))) + 3);
+                    }
+#pragma unroll
+                    for (int u = 0; u < 8; u++) {
+                        const int z = (g0 + u) & 63;
+                        if (q < lane_of(ncs, z))
+                            sring[lane_of(s_lo, z) + ((lane_of(tkn, z) + q) & lane_of(s_fm, z))] =
+                                make_uint4((uint32_t)ex[u], (uint32_t)(ex[u] >> 32), er[u], 0u);
+                        if (q < lane_of(nct, z)) cring[lane_of(t_co, z) + ((lane_of(pk, z) + q) & lane_of(t_fm, z))] = dc[u];
+                    }
+                }
+            }
+            tkn = ntail;
+            pk = npk;
+        }
+        // every workgroup has arrived
+        unsigned long long v = ld_dev(wordg);
+        spins = 0;
+        while (!stuck && (v & 0xFFFFull) < (unsigned long long)NB) {
+            if (++spins > kSpinLimit) stuck = true;
+            v = ld_dev(wordg);
+        }
+        const uint32_t nxt = ld_dev(nxtw);
+        done += ld_dev(outw);
+        if (w == 0 && j == 0 && !stuck) {
+            const int r5 = (int)((widx + 2) % 3u);
+            st_dev(reinterpret_cast<unsigned long long *>(d.gd_sync) + r5, 0ull);
+            st_dev(d.gd_sync + 6 + r5, kNever);
+            st_dev(d.gd_sync + 9 + r5, 0u);
+        }
+        cbar();
+        widx++;
+        if (stuck) {
+            state = kRunWatchdog;
+        } else if (done == (uint32_t)d.T) {
+            state = kRunOk;
+        } else if (v >> 32) {
+            state = kRunMaxCycles;
+        } else if (nxt == kNever) {
+            state = kRunDeadlock;
+        } else {
+            T0 = nxt;
+        }
+        if (state == kRunRunning && (uint64_t)T0 > d.max_cycles) state = kRunMaxCycles;
+        if (state == kRunRunning && local_cycles > d.watchdog) state = kRunWatchdog;
+    }
+    if (ht) {
+        d.tx_lines[t_link] = tx;
+        d.busy[t_link] = tx;  // one line per cycle at most: busy cycles = lines
+    }
+    const uint32_t last = ~wave_min(~maxcomp);
+    if (j == 0) {
+        if (last) atomicMax(&d.makespan[0], last);
+        atomicMax(&d.status[0], state);
+        atomicMax(reinterpret_cast<unsigned long long *>(&d.cycles[0]), (unsigned long long)local_cycles);
+    }
+}
+
 }  // namespace
 
 hipError_t launch_grid_any(const DevNet &d, hipStream_t st) {
@@ -1546,7 +1905,9 @@ hipError_t launch_grid_any(const DevNet &d, hipStream_t st) {
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     const void *k;
-    if (d.gd_window > 0)
+    if (d.gd_wave)
+        k = d.arb == 0 ? (const void *)engine_gridv<0> : (const void *)engine_gridv<1>;
+    else if (d.gd_window > 0)
         k = d.arb == 0 ? (const void *)engine_gridw<0> : (const void *)engine_gridw<1>;
     else if (d.gd_one)
         k = d.arb == 0 ? (d.has_preds ? (const void *)engine_grid1<0, true> : (const void *)engine_grid1<0, false>)

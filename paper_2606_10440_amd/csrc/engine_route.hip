@@ -261,7 +261,7 @@ __device__ __forceinline__ void route_cycles(const DevNet &d, unsigned char *sme
                 const bool rdy = e[0].y <= t;
                 next = rdy ? kNever : e[0].y;
                 nf = rdy ? 1u : 0u;
-                ejm = rdy & (h == rsink) ? 1u : 0u;
+                ejm = (rdy & (h == rsink)) ? 1u : 0u;
                 if (rdy & (h != rsink)) {
                     post[pslot] = make_uint2(e[0].x, e[0].c >> rbits);
                     atomicOr(&word[obase + h], pbit);

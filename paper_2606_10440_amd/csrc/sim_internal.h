@@ -173,7 +173,8 @@ struct DevNet {
     const int32_t *gd_fptr, *gd_fown;  // [gd_nb+1] CSR: the flows each workgroup keeps counters of
     uint32_t *gd_pub;         // [4*nl] appended counts (cycle parity 0, 1), popped counts (0, 1)
     unsigned long long *gd_dslot;  // [2*nflows] delivered counts: (first cycle valid << 32) | count
-    uint32_t *gd_sync;        // [16] arrival words [3 x 64 bit], next-cycle offers [3]
+    uint32_t *gd_sync;        // [16] arrival words [3 x 64 bit], next-cycle offers [3],
+                              //   lines completed [3]
     // one-line-per-cycle form (every bandwidth 1; one source and one target
     // side per thread, in registers)
     int32_t gd_one;
@@ -183,6 +184,11 @@ struct DevNet {
     int32_t gd_window;
     int32_t gd_sring_max, gd_cring_max;  // most LDS ring entries of one workgroup's source / target sides
     const int32_t *gd_sro, *gd_tro;      // [nl] offset of a lane's mirrored entries / credit cycles
+    // one wavefront per workgroup (gd_wave): lines carry their route (rt_code,
+    // rt_bits); post slot of a lane's FIFO (its head node's in-port table
+    // offset plus its port) and first target side of that node, per lane
+    int32_t gd_wave;
+    const int32_t *gd_pslot, *gd_tbase;
     int32_t gd_inl_max;       // most in-port table entries of one workgroup
     const int32_t *gd_toff;   // [nl] offset of a lane's tail node in its workgroup's in-port table
     const int32_t *gd_iptr, *gd_inl;  // [gd_nb+1] CSR: per node of the workgroup, for each input
