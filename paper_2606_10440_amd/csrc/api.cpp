@@ -834,6 +834,8 @@ sim_status finish_load(sim_ctx *c, Ranges &R) {
     struct WaveLayout {
         bool ok = false;
         bool lineup = false;  // the shift loop: paths of links on consecutive lanes
+        bool chain = false;   // the chain loop: one flow on and one out per link
+        int32_t maxnp = 0;
         int32_t G = 0, W = 0, nfs = 0;
         int32_t nblk = 0, wpb = 0;
         int64_t o_word = 0, o_red = 0, o_deliv = 0, o_req = 0, o_gnt = 0, o_gdep = 0, bytes = 0;
@@ -841,7 +843,8 @@ sim_status finish_load(sim_ctx *c, Ranges &R) {
     WaveLayout wv;
     std::vector<uint32_t> wv_lfb, wv_lfx;
     std::vector<int32_t> wv_feed, wv_nfeed, wv_sc, r_lf, pd_dix, blk_wave, blk_off;
-    std::vector<uint32_t> wv_duo;
+    std::vector<uint32_t> wv_duo, wv_fmask;
+    std::vector<int32_t> wv_ej;
     constexpr int64_t kWaveBlockLds = 160 * 1024;  // LDS of a compute unit
     // compute units of the current device (256 on MI355X)
     int32_t wave_blocks = 256;
@@ -923,6 +926,26 @@ sim_status finish_load(sim_ctx *c, Ranges &R) {
                 if (feeders[i].size() > 1 || (feeders[i].size() == 1 && feeders[i][0] != i - 1)) wv.lineup = false;
                 if (c->arb == SIM_ARB_LOWEST_ID && bmax > 1 && __builtin_popcount(tm) > 1) wv.lineup = false;
                 wv_duo[i] = tm;
+            }
+            // The chain loop: one flow at most goes on from each link and one at
+            // most leaves the network there.
+            wv.chain = wv.lineup;
+            wv_fmask.assign(nl, 0u);
+            wv_ej.assign(nl, 0);
+            for (int32_t i = 0; i < nl && wv.chain; i++) {
+                if (__builtin_popcount(wv_duo[i]) > 1 || (int32_t)lflows[i].size() - __builtin_popcount(wv_duo[i]) > 1)
+                    wv.chain = false;
+                for (size_t q = 0; q < lflows[i].size(); q++)
+                    if (!((wv_duo[i] >> q) & 1u)) wv_ej[i] = (int32_t)q;
+                if (!feeders[i].empty())  // the flow that the lane below sends on
+                    for (size_t q = 0; q < lflows[i - 1].size(); q++)
+                        if ((wv_duo[i - 1] >> q) & 1u)
+                            wv_fmask[i] = (wv_duo[i] >> lf_index(i, lflows[i - 1][q])) & 1u ? 0xFFFFFFFFu : 0xFFFFFFFEu;
+            }
+            for (int64_t j = 0; j < nr; j++) wv.maxnp = std::max(wv.maxnp, r_pd[j + 1] - r_pd[j]);
+            if (const char *ev = std::getenv("SIMGPU_WAVE_LOOP")) {
+                if (!std::strcmp(ev, "shift")) wv.chain = false;  // tests: the shift loop on such graphs
+                if (!std::strcmp(ev, "general")) wv.chain = false;
             }
             if (const char *ev = std::getenv("SIMGPU_WAVE_LOOP"))
                 if (!std::strcmp(ev, "general")) wv.lineup = false;  // tests: the arbitration loops on such graphs
@@ -1594,7 +1617,7 @@ sim_status finish_load(sim_ctx *c, Ranges &R) {
         // (+ one word: the request list is 8-byte aligned)
         const int64_t act = 4 * ((nsrc_all + 31) / 32 + nsrc_all + (int64_t)m + 1) + 8 * rcap + 4 * scap;
         const int64_t room = kLds - 1024;  // room for the static LDS
-        d.wg_act = (act <= room / 2 && !wg_scan) ? (int32_t)act : 0;
+        d.wg_act = (act <= (c->S <= wave_blocks ? room : room / 2) && !wg_scan) ? (int32_t)act : 0;
         d.wg_rcap = (int32_t)rcap;
         d.wg_scap = (int32_t)scap;
         const int64_t words = 7 * (int64_t)m + nsrc_all + 2 * (int64_t)s_link.size();
@@ -1636,6 +1659,8 @@ sim_status finish_load(sim_ctx *c, Ranges &R) {
     d.wv_wpb = wv.wpb;
     d.wv_nfs = wv.nfs;
     d.wv_lineup = wv.lineup ? 1 : 0;
+    d.wv_chain = wv.chain ? 1 : 0;
+    d.wv_maxnp = wv.maxnp;
     d.o_wword = (int32_t)wv.o_word;
     d.o_wred = (int32_t)wv.o_red;
     d.o_wdeliv = (int32_t)wv.o_deliv;
@@ -1838,6 +1863,10 @@ sim_status finish_load(sim_ctx *c, Ranges &R) {
         uint32_t *tmp_wv_lfb, *tmp_wv_lfx, *tmp_wv_duo;
         if (wv_duo.empty()) wv_duo.push_back(0);
         UP(wv_duo, wv_duo);
+        uint32_t *tmp_wv_fmask;
+        int32_t *tmp_wv_ej;
+        UP(wv_fmask, wv_fmask);
+        UP(wv_ej, wv_ej);
         int32_t *tmp_wv_feed, *tmp_wv_nfeed, *tmp_wv_sc, *tmp_r_lf, *tmp_pd_dix;
         UP(wv_lfb, wv_lfb);
         UP(wv_lfx, wv_lfx);

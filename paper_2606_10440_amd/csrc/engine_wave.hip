@@ -188,6 +188,20 @@ __device__ __forceinline__ void sort_net(K (&a)[N]) {
                     if (i + j + k < N && (i + j) / (2 * p) == (i + j + k) / (2 * p)) cex(a[i + j], a[i + j + k]);
 }
 
+// Descending sort of words (the words that are not 0 stay in their order).
+template <int N>
+__device__ __forceinline__ void sort_desc(uint32_t (&a)[N]) {
+#pragma unroll
+    for (int p = 1; p < N; p <<= 1)
+#pragma unroll
+        for (int k = p; k >= 1; k >>= 1)
+#pragma unroll
+            for (int j = k % p; j + k < N; j += 2 * k)
+#pragma unroll
+                for (int i = 0; i < k; i++)
+                    if (i + j + k < N && (i + j) / (2 * p) == (i + j + k) / (2 * p)) cex(a[i + j + k], a[i + j]);
+}
+
 // a, b ascending -> a = the N smallest of both, ascending.
 template <typename K, int N>
 __device__ __forceinline__ void merge_low(K (&a)[N], const K (&b)[N]) {
@@ -724,7 +738,569 @@ __global__ void __launch_bounds__(64 * kWaveMaxWpb) engine_wave(DevNet d) {
             if (sbad & on) state = kRunInternal;
         }
     };
-    if (lined) {
+    // Chain loop, one line per cycle: lined-up graphs where at most one flow
+    // goes on from a link and at most one leaves the network there.  Then a
+    // line needs no flow number: an entry word is the complement of the line
+    // id with bit 0 = the line goes on, so that "no line" is 0, the lowest id
+    // is the largest word, and a word from the lane below becomes this lane's
+    // by one AND with a lane constant (no feeder: 0; its lines leave here:
+    // all but bit 0).  What a lane of the wave decides about its neighbour --
+    // the line was taken -- is a bit of a wave mask shifted by one lane.
+    // The entry behind the head is read as a cycle begins and the next cycle's
+    // delivered count right after the completions, so no LDS round trip is
+    // waited for; decisions are wave masks in scalar registers.  The common cycle checks
+    // only that every live scenario moved a line; a scenario that did not
+    // jumps, ends (its lines were all gone one cycle before) or deadlocks in
+    // slow().  MP: some range waits on more than one flow; then the one that
+    // held the stream back last is polled, and all are read when it lets go.
+    // Bound: the instructions of one cycle (a lone wave issues one per four
+    // clocks).  Per cycle of a lone wave on the ring all-reduce sweep: 178
+    // instructions and 453 ns in the loop above, WAVE_INSTR and WAVE_NS here.
+    auto chain1 = [&](auto mp_tag) {
+        constexpr bool MP = decltype(mp_tag)::value;
+        typedef __attribute__((address_space(3))) uint32_t *L32;
+        typedef __attribute__((address_space(3))) unsigned long long *L64;
+        const L64 r0 = (L64) reinterpret_cast<unsigned long long *>(ring);
+        const L64 rb = r0 + rbase, re = rb + cap, trash = r0 + ring_trash;
+        const L32 dl0 = (L32)deliv;
+        const L32 always = (L32)(word + w);  // holds the largest count
+        const uint32_t fmask = on ? d.wv_fmask[i] : 0u;
+        const L32 dej = dl0 + (mydx + (on ? (uint32_t)d.wv_ej[i] : 0u));
+        const uint32_t upq = on ? d.wv_duo[i] : 0u;
+        const uint32_t sm_lo = (uint32_t)smask, sm_hi = (uint32_t)(smask >> 32);
+        L64 pt = rb, ph = rb;                   // next slot, head slot
+        uint32_t free = cap;                    // free slots
+        uint32_t hy = kNever;                   // the head's ready cycle
+        uint32_t lastf = 0;                     // round-robin: not 0, the last line appended came from the feeder
+        bool ne = false;                        // the FIFO holds a line
+        uint32_t tx32 = 0, iters = 0, dvp = 0;
+        uint32_t tinc = live ? 1u : 0u;
+        // stream: word of line 0 of the range, minus the range's length, minus
+        // the lines sent, polled predecessor (base, counter address), lines
+        // the other predecessors allow (MP)
+        uint32_t c0 = 0, nlen = 1, no = 0, pbp = 0xFFFFFFFFu, limo = 0xFFFFFFFFu;
+        L32 da = always;
+        uint32_t ixr[MP ? 8 : 1], pbr[MP ? 8 : 1];
+        auto set_range = [&]() {  // (selects only: stores under a branch here kept these in scratch memory)
+            const bool has = R < rend;
+            const bool waits = has & (cur.np > 0u);
+            no = 0u;
+            c0 = has ? (~cur.start << kXs) | ((upq >> cur.lf) & 1u) : 0u;
+            nlen = has ? 0u - cur.len : 1u;
+            da = waits ? dl0 + cur.ix0 : always;
+            pbp = waits ? cur.pb0 : has ? 0u : 0xFFFFFFFFu;  // (no count is above the last)
+            if constexpr (MP) {
+                limo = (has & (cur.np > 1u)) ? 0u : 0xFFFFFFFFu;
+#pragma unroll
+                for (int q = 0; q < 8; q++) {
+                    const bool is = has & ((uint32_t)q < cur.np);
+                    ixr[q] = is ? (uint32_t)d.pd_dix[cur.pd0 + q] : 0u;
+                    pbr[q] = is ? d.pd_base[cur.pd0 + q] : 0u;
+                }
+                vm_drain();
+            }
+        };
+        set_range();
+        dvp = *da;
+        // the lowest and second lowest allowance over all predecessors
+        auto recheck = [&]() {
+            if constexpr (MP) {
+                uint32_t a0 = 0xFFFFFFFFu, a1 = 0xFFFFFFFFu;
+                auto take = [&](uint32_t ix, uint32_t pb) {
+                    const uint32_t a = pred_allows<CH>(deliv[ix], pb);
+                    const bool lo = a < a0;
+                    a1 = lo ? a0 : min(a1, a);
+                    da = lo ? dl0 + ix : da;
+                    pbp = lo ? pb : pbp;
+                    a0 = lo ? a : a0;
+                };
+#pragma unroll
+                for (int q = 0; q < 8; q++)
+                    if ((uint32_t)q < cur.np) take(ixr[q], pbr[q]);
+                if (cur.np > 8u) {
+                    for (uint32_t q = 8; q < cur.np; q++) take((uint32_t)d.pd_dix[cur.pd0 + (int)q], d.pd_base[cur.pd0 + (int)q]);
+                    vm_drain();
+                }
+                limo = a1;
+            }
+        };
+        // cycles until some live scenario passes the cycle guard or the watchdog
+        auto budget_now = [&]() -> uint32_t {
+            uint32_t v = 0x3FFFFFFFu;
+            if (live) v = min(v, min(maxc - t, wdog - min(wdog, processed + iters)));
+#pragma unroll
+            for (int sh = 32; sh >= 1; sh >>= 1) v = min(v, (uint32_t)__shfl_xor((int)v, sh));
+            return (uint32_t)__builtin_amdgcn_readfirstlane((int)v) + 1u;
+        };
+        // scenarios past the cycle guard or the watchdog end; t is one past
+        // the cycle just processed there
+        auto guard = [&]() {
+            const bool act = live & (ne | (R < rend));
+            const bool sact = (__ballot(act) & smask) != 0ull;
+            const bool past = live & ((t > maxc) | (processed + iters > wdog));
+            if (past) {
+                state = !sact ? kRunOk : t > maxc ? kRunMaxCycles : kRunWatchdog;
+                t -= 1u;
+                processed += iters;
+                live = false;
+            }
+        };
+        auto slow = [&](bool idle) {
+            const bool act = live & (ne | (R < rend));
+            const bool sact = (__ballot(act) & smask) != 0ull;
+            const uint32_t nxt = (idle & ne & (hy > t)) ? hy : kNever;
+            cbar();
+            atomicMin(&red[nxt != kNever ? (uint32_t)g : 64u + (uint32_t)w], nxt);
+            cbar();
+            const uint32_t rv = red[g];
+            cbar();
+            red[i == 0 ? (uint32_t)g : 64u + (uint32_t)w] = kNever;
+            if (idle) {
+                if (!sact) {  // its last line left in the cycle before
+                    state = kRunOk;
+                    processed += iters - 1u;
+                    t -= 1u;
+                    live = false;
+                } else if ((rv == kNever) | (rv > maxc)) {
+                    state = rv == kNever ? kRunDeadlock : kRunMaxCycles;
+                    processed += iters;
+                    live = false;
+                } else {
+                    t = rv;
+                }
+            } else {
+                t += live ? 1u : 0u;
+            }
+            guard();
+            tinc = live ? 1u : 0u;
+        };
+        uint32_t mostx = 0, hu = 0, hx = 0;  // the head's word if it goes on / if it leaves, else 0
+        const uint32_t Tm = Tu - 1u;
+        uint32_t still = live ? 0u : 1u;     // not 0: the lane's scenario has ended
+        L64 ph1 = rb + 1 == re ? rb : rb + 1;
+        unsigned long long n1 = 0ull;        // the entry behind the head (with two lines or more)
+        hy = kNever;                         // (an empty FIFO's head is never ready)
+        while (__ballot(live) != 0ull) {
+            uint32_t left = budget_now();
+            const uint32_t left0 = left;
+            unsigned long long im;
+            for (;;) {
+                // -------------------------------------------------- stream ranges
+                bool t1 = dvp > pbp - (CH ? 0u : no);
+                bool ends = no == nlen;
+                if constexpr (MP) ends = ends | (t1 & (limo <= 0u - no));
+                if (__builtin_expect(__ballot(ends) != 0ull, 0)) {
+                    if (no == nlen) {
+                        o = 0u - no;
+                        next_range();
+                        set_range();
+                    }
+                    if constexpr (MP) {
+                        if ((cur.np > 1u) & (R < rend)) recheck();
+                    }
+                    dvp = *da;
+                    t1 = dvp > pbp - (CH ? 0u : no);
+                    if constexpr (MP) t1 = t1 & (limo > 0u - no);
+                }
+                // -------------------------------------------------- heads
+                const bool rdy = hy <= t;
+                const uint32_t uw = rdy ? hu : 0u, ew = rdy ? hx : 0u;  // offered to the lane above; leaving
+                uint32_t fe = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)uw, 0x138, 0xF, 0xF, true);
+                asm volatile("" : "+v"(fe));  // (the shift stays on a path that every lane takes)
+                fe &= fmask;
+                const uint32_t ready = t + L;
+                if (ew != 0u) {
+                    const uint32_t x = 0x1FFFFFFu - (ew >> kXs);
+                    mostx = max(mostx, x);
+                    comp[min(x, Tm)] = t + 1u;
+                }
+                // (by every lane, also one that adds nothing: the number of LDS
+                // operations in flight is then known, and the wait for the
+                // entry read before does not include this one)
+                __hip_atomic_fetch_add(dej, ew != 0u ? 1u : 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
+                cbar();
+                dvp = *da;  // as of the next cycle's start
+                // -------------------------------------------------- arbitration
+                const uint32_t sx = t1 ? c0 + (no << kXs) : 0u;
+                bool fw;  // the feeder's line comes first
+                if constexpr (ARB == 0) fw = fe > sx;
+                else fw = (fe != 0u) & ((sx == 0u) | (lastf == 0u));
+                const uint32_t win = ARB == 0 ? max(fe, sx) : (fw ? fe : sx);
+                const uint32_t aw = min(win, free);         // not 0: a line is appended
+                const uint32_t gf = fw ? aw : 0u, gs = fw ? 0u : aw;
+                uint32_t got = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)gf, 0x130, 0xF, 0xF, true);
+                asm volatile("" : "+v"(got));
+                const bool app = aw != 0u;
+                *(app ? pt : trash) = ((unsigned long long)ready << 32) | win;
+                const uint32_t pw = min(uw, got) | ew;      // not 0: the head leaves
+                // -------------------------------------------------- state
+                // the head: kept, the entry behind it, or the line just appended
+                const bool pop = pw != 0u;
+                const bool take1 = pop & ((int)free <= (int)cap - 2);
+                free += pop ? 1u : 0u;
+                const bool takea = app & (free == cap);
+                free -= app ? 1u : 0u;
+                uint32_t hw = hu | hx;
+                hw = pop ? 0u : hw;
+                hy = pop ? kNever : hy;
+                hw = take1 ? (uint32_t)n1 : hw;
+                hy = take1 ? (uint32_t)(n1 >> 32) : hy;
+                hw = takea ? win : hw;
+                hy = takea ? ready : hy;
+                ph = pop ? ph1 : ph;
+                ph1 = ph + 1 == re ? rb : ph + 1;
+                // (the old n1 is used up here: its registers take the new one,
+                // whose arrival a copy would wait for)
+                asm volatile("" : "+v"(hw), "+v"(hy));
+                cbar();
+                n1 = *ph1;
+                const uint32_t um = 0u - (hw & 1u);
+                hu = hw & um;
+                hx = hw & ~um;
+                const L64 pt1 = pt + 1 == re ? rb : pt + 1;
+                pt = app ? pt1 : pt;
+                tx32 += app ? 1u : 0u;
+                no -= gs != 0u ? 1u : 0u;
+                if constexpr (ARB == 1) lastf = app ? gf : lastf;
+                // -------------------------------------------------- time
+                left--;
+                const unsigned long long dm = __ballot((pw | gs) != 0u);
+                uint32_t moved = ((uint32_t)dm & sm_lo) | still;
+                moved = ((uint32_t)(dm >> 32) & sm_hi) | moved;
+                im = __ballot(moved == 0u);
+                if (__builtin_expect(im != 0ull, 0)) break;
+                t += tinc;
+                if (__builtin_expect(left == 0u, 0)) break;
+            }
+            // a live scenario moved nothing, or the guard is due
+            iters += left0 - left;
+            ne = free != cap;
+            if (im != 0ull) {
+                slow(__builtin_amdgcn_inverse_ballot_w64(im));
+            } else {
+                guard();
+                tinc = live ? 1u : 0u;
+            }
+            still = live ? 0u : 1u;
+        }
+        bad = (Tu != 0u) & (mostx >= Tu);
+        tx += tx32;
+        busy += tx32;  // one line per cycle at most
+        if (__ballot(bad) != 0ull) {  // engine fault: end the faulty scenarios
+            const bool sbad = (__ballot(bad) & smask) != 0ull;
+            if (sbad & on) state = kRunInternal;
+        }
+    };
+    // Chain loop for several lines per cycle (lowest id): the same words, the
+    // first BMW entries of a FIFO read from the ring at the end of each cycle.
+    // The feeder's lines and the stream's arrive as two descending lists of
+    // words; a bitonic merge gives the first BMW of both in order, the smallest
+    // word appended tells how many of the feeder's lines it took (those at or
+    // above it), and one shift hands that number back.
+    auto chain = [&](auto bmw_tag, auto mp_tag) {
+        constexpr int BMW = decltype(bmw_tag)::value;
+        constexpr bool MP = decltype(mp_tag)::value;
+        typedef __attribute__((address_space(3))) uint32_t *L32;
+        typedef __attribute__((address_space(3))) unsigned long long *L64;
+        const L64 r0 = (L64) reinterpret_cast<unsigned long long *>(ring);
+        const L64 rb = r0 + rbase, trash = r0 + ring_trash;
+        const L32 dl0 = (L32)deliv;
+        const L32 always = (L32)(word + w);  // holds the largest count
+        const uint32_t fmask = on ? d.wv_fmask[i] : 0u;
+        const L32 dej = dl0 + (mydx + (on ? (uint32_t)d.wv_ej[i] : 0u));
+        const uint32_t upq = on ? d.wv_duo[i] : 0u;
+        const uint32_t sm_lo = (uint32_t)smask, sm_hi = (uint32_t)(smask >> 32);
+        const uint32_t Tm = Tu - 1u, bu = (uint32_t)b;
+        uint32_t it = 0, ih = 0, occ = 0;  // next slot, head slot (entries from the ring's start), lines held
+        uint32_t hw[BMW], hy[BMW];         // first entries (k < occ)
+        uint32_t tx32 = 0, busy32 = 0, iters = 0, dvp = 0, mostx = 0;
+        uint32_t tinc = live ? 1u : 0u, still = live ? 0u : 1u;
+        uint32_t c0 = 0, nlen = 1, no = 0, pbp = 0xFFFFFFFFu, limo = 0xFFFFFFFFu;
+        L32 da = always;
+        uint32_t ixr[MP ? 8 : 1], pbr[MP ? 8 : 1];
+#pragma unroll
+        for (int k = 0; k < BMW; k++) {
+            hw[k] = 0u;
+            hy[k] = kNever;
+        }
+        auto set_range = [&]() {  // (as in chain1)
+            const bool has = R < rend;
+            const bool waits = has & (cur.np > 0u);
+            no = 0u - (has ? o : 0u);
+            c0 = has ? (~cur.start << kXs) | ((upq >> cur.lf) & 1u) : 0u;
+            nlen = has ? 0u - cur.len : 1u;
+            da = waits ? dl0 + cur.ix0 : always;
+            pbp = waits ? cur.pb0 : has ? 0u : 0xFFFFFFFFu;
+            if constexpr (MP) {
+                limo = (has & (cur.np > 1u)) ? 0u : 0xFFFFFFFFu;
+#pragma unroll
+                for (int q = 0; q < 8; q++) {
+                    const bool is = has & ((uint32_t)q < cur.np);
+                    ixr[q] = is ? (uint32_t)d.pd_dix[cur.pd0 + q] : 0u;
+                    pbr[q] = is ? d.pd_base[cur.pd0 + q] : 0u;
+                }
+                vm_drain();
+            }
+        };
+        set_range();
+        dvp = *da;
+        auto recheck = [&]() {  // (as in chain1)
+            if constexpr (MP) {
+                uint32_t a0 = 0xFFFFFFFFu, a1 = 0xFFFFFFFFu;
+                auto take = [&](uint32_t ix, uint32_t pb) {
+                    const uint32_t a = pred_allows<CH>(deliv[ix], pb);
+                    const bool lo = a < a0;
+                    a1 = lo ? a0 : min(a1, a);
+                    da = lo ? dl0 + ix : da;
+                    pbp = lo ? pb : pbp;
+                    a0 = lo ? a : a0;
+                };
+#pragma unroll
+                for (int q = 0; q < 8; q++)
+                    if ((uint32_t)q < cur.np) take(ixr[q], pbr[q]);
+                if (cur.np > 8u) {
+                    for (uint32_t q = 8; q < cur.np; q++) take((uint32_t)d.pd_dix[cur.pd0 + (int)q], d.pd_base[cur.pd0 + (int)q]);
+                    vm_drain();
+                }
+                limo = a1;
+            }
+        };
+        auto budget_now = [&]() -> uint32_t {
+            uint32_t v = 0x3FFFFFFFu;
+            if (live) v = min(v, min(maxc - t, wdog - min(wdog, processed + iters)));
+#pragma unroll
+            for (int sh = 32; sh >= 1; sh >>= 1) v = min(v, (uint32_t)__shfl_xor((int)v, sh));
+            return (uint32_t)__builtin_amdgcn_readfirstlane((int)v) + 1u;
+        };
+        auto guard = [&]() {
+            const bool act = live & ((occ != 0u) | (R < rend));
+            const bool sact = (__ballot(act) & smask) != 0ull;
+            const bool past = live & ((t > maxc) | (processed + iters > wdog));
+            if (past) {
+                state = !sact ? kRunOk : t > maxc ? kRunMaxCycles : kRunWatchdog;
+                t -= 1u;
+                processed += iters;
+                live = false;
+            }
+        };
+        auto slow = [&](bool idle) {
+            const bool act = live & ((occ != 0u) | (R < rend));
+            const bool sact = (__ballot(act) & smask) != 0ull;
+            const uint32_t nxt = (idle & (occ != 0u) & (hy[0] > t)) ? hy[0] : kNever;
+            cbar();
+            atomicMin(&red[nxt != kNever ? (uint32_t)g : 64u + (uint32_t)w], nxt);
+            cbar();
+            const uint32_t rv = red[g];
+            cbar();
+            red[i == 0 ? (uint32_t)g : 64u + (uint32_t)w] = kNever;
+            if (idle) {
+                if (!sact) {  // its last line left in the cycle before
+                    state = kRunOk;
+                    processed += iters - 1u;
+                    t -= 1u;
+                    live = false;
+                } else if ((rv == kNever) | (rv > maxc)) {
+                    state = rv == kNever ? kRunDeadlock : kRunMaxCycles;
+                    processed += iters;
+                    live = false;
+                } else {
+                    t = rv;
+                }
+            } else {
+                t += live ? 1u : 0u;
+            }
+            guard();
+        };
+        // slot k entries after slot v of the ring
+        auto slot = [&](uint32_t v, uint32_t k) -> uint32_t {
+            const uint32_t a = v + k;
+            return min(a, a - cap);  // (a - cap wraps to a large number below cap; k <= cap)
+        };
+        auto cexd = [](uint32_t &a, uint32_t &b2) {
+            const uint32_t hi = max(a, b2), lo = min(a, b2);
+            a = hi;
+            b2 = lo;
+        };
+        while (__ballot(live) != 0ull) {
+            uint32_t left = budget_now();
+            const uint32_t left0 = left;
+            unsigned long long im;
+            for (;;) {
+                // -------------------------------------------------- stream offers
+                const uint32_t rem = no - nlen;  // lines left in the range (0: no stream)
+                const uint32_t want = R < rend ? min(bu, rem) : 0u;
+                auto avail = [&]() -> uint32_t {
+                    const uint32_t q0 = pbp - (CH ? 0u : no);
+                    return dvp > q0 ? (CH ? 0xFFFFFFFFu : dvp - q0) : 0u;
+                };
+                uint32_t av = avail();
+                if constexpr (MP) {
+                    const uint32_t oo = 0u - no;
+                    if (__builtin_expect(__ballot((want != 0u) & (av != 0u) & (limo - min(limo, oo) < want)) != 0ull, 0)) {
+                        if ((cur.np > 1u) & (R < rend)) recheck();
+                        dvp = *da;
+                        av = avail();
+                    }
+                    av = min(av, limo - min(limo, oo));
+                }
+                uint32_t nS = min(want, av);
+                uint32_t sw[BMW];
+                const uint32_t cw = c0 + (no << kXs);
+#pragma unroll
+                for (int k = 0; k < BMW; k++) sw[k] = (uint32_t)k < nS ? cw - ((uint32_t)k << kXs) : 0u;
+                if (__builtin_expect(__ballot((nS == rem) & (nS < bu) & (R + 1 < rend)) != 0ull, 0)) {
+                    // the offer runs into the ranges after the current one
+                    if ((nS == rem) & (nS < bu) & (R + 1 < rend) & live) {
+                        int sR = R + 1;
+                        WRange sr;
+                        while (sR < rend && nS < bu) {
+                            load_wrange(d, sR, sr);
+                            const uint32_t n = released_direct<CH>(d, sr, min(bu - nS, sr.len), deliv);
+                            const uint32_t c1 = (~sr.start << kXs) | ((upq >> sr.lf) & 1u);
+#pragma unroll
+                            for (int k = 0; k < BMW; k++)
+                                if (((uint32_t)k >= nS) & ((uint32_t)k < nS + n)) sw[k] = c1 - (((uint32_t)k - nS) << kXs);
+                            nS += n;
+                            if (n < sr.len) break;
+                            sR++;
+                        }
+                    }
+                }
+                // -------------------------------------------------- heads
+                // (ready times never decrease along a FIFO)
+                const uint32_t nh = min(bu, occ);
+                uint32_t uw[BMW], ew[BMW];  // ready entries that go on / that leave, else 0
+                uint32_t fe[BMW];
+#pragma unroll
+                for (int k = 0; k < BMW; k++) {
+                    const uint32_t v = (((uint32_t)k < nh) & (hy[k] <= t)) ? hw[k] : 0u;
+                    uw[k] = (v & 1u) != 0u ? v : 0u;
+                    ew[k] = (v & 1u) != 0u ? 0u : v;
+                    fe[k] = uw[k];
+                }
+                // the entries that go on, those that leave squeezed out
+                if constexpr (BMW == 2) {
+                    cexd(fe[0], fe[1]);
+                } else {
+                    sort_desc(fe);
+                }
+#pragma unroll
+                for (int k = 0; k < BMW; k++) {
+                    fe[k] = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)fe[k], 0x138, 0xF, 0xF, true);
+                    asm volatile("" : "+v"(fe[k]));  // (the shift stays on a path that every lane takes)
+                    fe[k] &= fmask;
+                }
+                // -------------------------------------------------- arbitration
+                const uint32_t room = min(bu, cap - occ);
+                uint32_t mw[BMW];  // the first BMW of both lists, descending
+#pragma unroll
+                for (int k = 0; k < BMW; k++) mw[k] = max(fe[k], sw[BMW - 1 - k]);
+#pragma unroll
+                for (int k = BMW / 2; k >= 1; k >>= 1)
+#pragma unroll
+                    for (int q = 0; q < BMW; q++)
+                        if ((q & k) == 0) cexd(mw[q], mw[q + k]);
+                const uint32_t ready = t + L;
+                uint32_t G = 0, thr = 0xFFFFFFFFu, gF = 0;
+#pragma unroll
+                for (int k = 0; k < BMW; k++) {
+                    const bool ap = ((uint32_t)k < room) & (mw[k] != 0u);
+                    G += ap ? 1u : 0u;
+                    thr = ap ? mw[k] : thr;
+                    *(ap ? rb + slot(it, (uint32_t)k) : trash) = ((unsigned long long)ready << 32) | mw[k];
+                }
+#pragma unroll
+                for (int k = 0; k < BMW; k++) gF += fe[k] >= thr ? 1u : 0u;
+                uint32_t got = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)gF, 0x130, 0xF, 0xF, true);
+                asm volatile("" : "+v"(got));
+                // -------------------------------------------------- departures
+                uint32_t gout = 0, ne = 0;
+                bool open = true;
+#pragma unroll
+                for (int k = 0; k < BMW; k++) {
+                    // the entry goes on and is among those taken, or leaves
+                    const bool up = (uw[k] != 0u) & (got != 0u);
+                    got -= up ? 1u : 0u;
+                    open = open & (up | (ew[k] != 0u));
+                    gout += open ? 1u : 0u;
+                    ew[k] = open ? ew[k] : 0u;
+                    ne += ew[k] != 0u ? 1u : 0u;
+                }
+                if (ne != 0u) {
+#pragma unroll
+                    for (int k = 0; k < BMW; k++)
+                        if (ew[k] != 0u) {
+                            const uint32_t x = 0x1FFFFFFu - (ew[k] >> kXs);
+                            mostx = max(mostx, x);
+                            comp[min(x, Tm)] = t + 1u;
+                        }
+                }
+                __hip_atomic_fetch_add(dej, ne, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
+                // -------------------------------------------------- state
+                const uint32_t gS = G - gF;
+                ih = slot(ih, gout);
+                it = slot(it, G);
+                occ += G - gout;
+                tx32 += G;
+                busy32 += G != 0u ? 1u : 0u;
+                no -= gS;
+                if (__builtin_expect(__ballot((gS != 0u) & (gS >= rem)) != 0ull, 0)) {
+                    if ((gS != 0u) & (gS >= rem)) {
+                        o = 0u - no;
+                        next_range();
+                        set_range();
+                    }
+                }
+                cbar();
+#pragma unroll
+                for (int k = 0; k < BMW; k++) {
+                    const unsigned long long v = rb[slot(ih, min((uint32_t)k, cap - 1u))];
+                    hw[k] = (uint32_t)v;
+                    hy[k] = (uint32_t)(v >> 32);
+                }
+                dvp = *da;
+                // -------------------------------------------------- time
+                left--;
+                const unsigned long long dm = __ballot((gout | gS) != 0u);
+                uint32_t moved = ((uint32_t)dm & sm_lo) | still;
+                moved = ((uint32_t)(dm >> 32) & sm_hi) | moved;
+                im = __ballot(moved == 0u);
+                if (__builtin_expect(im != 0ull, 0)) break;
+                t += tinc;
+                if (__builtin_expect(left == 0u, 0)) break;
+            }
+            // a live scenario moved nothing, or the guard is due
+            iters += left0 - left;
+            if (im != 0ull) slow(__builtin_amdgcn_inverse_ballot_w64(im));
+            else guard();
+            tinc = live ? 1u : 0u;
+            still = live ? 0u : 1u;
+        }
+        bad = (Tu != 0u) & (mostx >= Tu);
+        tx += tx32;
+        busy += busy32;
+        if (__ballot(bad) != 0ull) {  // engine fault: end the faulty scenarios
+            const bool sbad = (__ballot(bad) & smask) != 0ull;
+            if (sbad & on) state = kRunInternal;
+        }
+    };
+    const bool chained = lined && d.wv_chain && (ARB == 0 || wbm <= 1);
+    if (chained && wbm <= 1) {
+        if (d.wv_maxnp <= 1) chain1(std::false_type{});
+        else chain1(std::true_type{});
+    } else if (chained) {
+        if constexpr (ARB == 0 && BM >= 2) {
+            auto run = [&](auto bmw_tag) {
+                if (d.wv_maxnp <= 1) chain(bmw_tag, std::false_type{});
+                else chain(bmw_tag, std::true_type{});
+            };
+            if (wbm <= 2 || BM == 2) run(std::integral_constant<int, 2>{});
+            else if constexpr (BM >= 4) {
+                if (wbm <= 4 || BM == 4) run(std::integral_constant<int, 4>{});
+                else if constexpr (BM >= 8) run(std::integral_constant<int, 8>{});
+            }
+        }
+    } else if (lined) {
         if (wbm <= 1) lineup(std::integral_constant<int, 1>{});
         else if constexpr (BM >= 2) {
             if (wbm <= 2 || BM == 2) lineup(std::integral_constant<int, 2>{});

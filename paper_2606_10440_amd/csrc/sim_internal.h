@@ -146,6 +146,11 @@ struct DevNet {
     int32_t wv_nfs;           // request-slot groups per target lane: feeders + the lane's own stream
     int32_t wv_lineup;        // shift loop: a lane's feeder is lane - 1, its next link lane + 1
     const uint32_t *wv_duo;   // [nl] shift loop: local flows bound for the next lane (bit q)
+    // chain loop: at most one flow goes on from a link and one leaves there
+    int32_t wv_chain;
+    int32_t wv_maxnp;         // most flows a range waits on
+    const uint32_t *wv_fmask; // [nl] mask of a word from the lane below (0: no feeder; ~1: its lines leave here)
+    const int32_t *wv_ej;     // [nl] local index of the flow that leaves the network at the lane
     int32_t o_wword, o_wred, o_wdeliv, o_wreq, o_wgnt, o_wgdep;  // LDS byte offsets after a wave's rings
     const int32_t *blk_wave;  // [wv_nblk*wv_wpb] wave of each slot, -1 if empty
     const int32_t *blk_off;   // [wv_nblk*wv_wpb] LDS byte offset of the slot's region
