@@ -754,8 +754,9 @@ __global__ void __launch_bounds__(64 * kWaveMaxWpb) engine_wave(DevNet d) {
     // slow().  MP: some range waits on more than one flow; then the one that
     // held the stream back last is polled, and all are read when it lets go.
     // Bound: the instructions of one cycle (a lone wave issues one per four
-    // clocks).  Per cycle of a lone wave on the ring all-reduce sweep: 178
-    // instructions and 453 ns in the loop above, WAVE_INSTR and WAVE_NS here.
+    // clocks).  Per cycle of a lone wave: 88 instructions and 235 ns on a mesh
+    // of 8 (434 ns in the loop above), 288 ns on the ring all-reduce sweep
+    // (178 instructions, 465 ns).
     auto chain1 = [&](auto mp_tag) {
         constexpr bool MP = decltype(mp_tag)::value;
         typedef __attribute__((address_space(3))) uint32_t *L32;
@@ -996,7 +997,9 @@ __global__ void __launch_bounds__(64 * kWaveMaxWpb) engine_wave(DevNet d) {
     // The feeder's lines and the stream's arrive as two descending lists of
     // words; a bitonic merge gives the first BMW of both in order, the smallest
     // word appended tells how many of the feeder's lines it took (those at or
-    // above it), and one shift hands that number back.
+    // above it), and one shift hands that number back.  Ring all-reduce sweep,
+    // ns per cycle of a lone wave: 500 at two lines (725 in the shift loop),
+    // 830 at four (1275).
     auto chain = [&](auto bmw_tag, auto mp_tag) {
         constexpr int BMW = decltype(bmw_tag)::value;
         constexpr bool MP = decltype(mp_tag)::value;
@@ -1226,6 +1229,18 @@ __global__ void __launch_bounds__(64 * kWaveMaxWpb) engine_wave(DevNet d) {
                     ew[k] = open ? ew[k] : 0u;
                     ne += ew[k] != 0u ? 1u : 0u;
                 }
+                __hip_atomic_fetch_add(dej, ne, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
+                // the next cycle's heads and delivered count, read before the rest
+                // of this cycle is done
+                cbar();
+                ih = slot(ih, gout);
+#pragma unroll
+                for (int k = 0; k < BMW; k++) {
+                    const unsigned long long v = rb[slot(ih, min((uint32_t)k, cap - 1u))];
+                    hw[k] = (uint32_t)v;
+                    hy[k] = (uint32_t)(v >> 32);
+                }
+                dvp = *da;
                 if (ne != 0u) {
 #pragma unroll
                     for (int k = 0; k < BMW; k++)
@@ -1235,10 +1250,8 @@ __global__ void __launch_bounds__(64 * kWaveMaxWpb) engine_wave(DevNet d) {
                             comp[min(x, Tm)] = t + 1u;
                         }
                 }
-                __hip_atomic_fetch_add(dej, ne, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
                 // -------------------------------------------------- state
                 const uint32_t gS = G - gF;
-                ih = slot(ih, gout);
                 it = slot(it, G);
                 occ += G - gout;
                 tx32 += G;
@@ -1249,16 +1262,9 @@ __global__ void __launch_bounds__(64 * kWaveMaxWpb) engine_wave(DevNet d) {
                         o = 0u - no;
                         next_range();
                         set_range();
+                        dvp = *da;
                     }
                 }
-                cbar();
-#pragma unroll
-                for (int k = 0; k < BMW; k++) {
-                    const unsigned long long v = rb[slot(ih, min((uint32_t)k, cap - 1u))];
-                    hw[k] = (uint32_t)v;
-                    hy[k] = (uint32_t)(v >> 32);
-                }
-                dvp = *da;
                 // -------------------------------------------------- time
                 left--;
                 const unsigned long long dm = __ballot((gout | gS) != 0u);
