@@ -43,11 +43,14 @@ def _run(cmd, verbose):
 # lane-varying operands are combined per wave by a DPP scan instead of a
 # scalar loop over the active lanes; the wave and lane engines, whose
 # lone wavefronts wait on LDS each simulated cycle, are scheduled for
-# instruction-level parallelism (measured: the wave engine 3-7 % and the
-# lane engine about 3 % less time per launch; the resident and grid
-# engines ran slower so)
+# instruction-level parallelism (measured: the lane engine about 3 % less
+# time per launch; the wave engine's loops, ns per cycle with the default /
+# iterative-ILP / max-ILP scheduler: ring sweep 271 / 291 / 268 at one line,
+# 881 / 826 / 822 at four, per-chunk 821 / 753 / 756 at four, tree sweep
+# 1521 / 1508 / 1436 at four, and the iterative one crashes the compiler on
+# small changes; the resident and grid engines ran slower so)
 EXTRA = {"engine_res.hip": ["-mllvm", "-amdgpu-atomic-optimizer-strategy=DPP"],
-         "engine_wave.hip": ["-mllvm", "-amdgpu-sched-strategy=iterative-ilp"],
+         "engine_wave.hip": ["-mllvm", "-amdgpu-sched-strategy=max-ilp"],
          "engine_lane.hip": ["-mllvm", "-amdgpu-sched-strategy=max-ilp"]}
 
 

@@ -97,6 +97,7 @@ struct WRange {
     uint32_t start, len, lf, np;
     int32_t pd0;
     uint32_t ix0, ix1, pb0, pb1;
+    uint32_t lim;  // lines that the predecessors after the second are known to allow
 };
 
 __device__ __forceinline__ void load_wrange(const DevNet &d, int R, WRange &r) {
@@ -110,6 +111,7 @@ __device__ __forceinline__ void load_wrange(const DevNet &d, int R, WRange &r) {
     r.pb0 = r.np > 0 ? d.pd_base[r.pd0] : 0u;
     r.ix1 = r.np > 1 ? (uint32_t)d.pd_dix[r.pd0 + 1] : 0u;
     r.pb1 = r.np > 1 ? d.pd_base[r.pd0 + 1] : 0u;
+    r.lim = 0u;
     vm_drain();
 }
 
@@ -121,34 +123,44 @@ __device__ __forceinline__ uint32_t pred_allows(uint32_t v, uint32_t bb) {
     return v > bb ? (CH ? 0xFFFFFFFFu : v - bb) : 0u;
 }
 
+// The lines of range r that its predecessors after the second allow.  Their
+// descriptors are in device memory: they are read only when a line beyond the
+// known allowance is asked for (delivered counts never fall).
+template <bool CH>
+__device__ __forceinline__ void read_lim(const DevNet &d, WRange &r, const uint32_t *deliv) {
+    uint32_t a = 0xFFFFFFFFu;
+    for (int idx = r.pd0 + 2; idx < r.pd0 + (int)r.np; idx++)
+        a = min(a, pred_allows<CH>(deliv[d.pd_dix[idx]], d.pd_base[idx]));
+    vm_drain();
+    r.lim = a;
+}
+
 // Lines of range r from offset o on whose predecessors have all been
 // delivered (a prefix: the counts only grow with o), capped at n.  dv0/dv1
 // hold the first two predecessors' delivered counts as of the cycle start.
 // CH: per-chunk dependencies (every base is the whole chunk's; no offset).
 template <bool CH>
-__device__ __forceinline__ uint32_t released_count(const DevNet &d, const WRange &r, uint32_t o, uint32_t n,
+__device__ __forceinline__ uint32_t released_count(const DevNet &d, WRange &r, uint32_t o, uint32_t n,
                                                    uint32_t dv0, uint32_t dv1, const uint32_t *deliv) {
     const uint32_t oo = CH ? 0u : o;
     n = r.np > 0 ? min(n, pred_allows<CH>(dv0, r.pb0 + oo)) : n;
     n = r.np > 1 ? min(n, pred_allows<CH>(dv1, r.pb1 + oo)) : n;
     if ((n != 0u) & (r.np > 2)) {
-        for (int idx = r.pd0 + 2; idx < r.pd0 + (int)r.np; idx++)
-            n = min(n, pred_allows<CH>(deliv[d.pd_dix[idx]], d.pd_base[idx] + oo));
-        vm_drain();
+        if (r.lim < o + n) read_lim<CH>(d, r, deliv);
+        n = min(n, r.lim - min(r.lim, o));
     }
     return n;
 }
 
 // Whether line o of range r is released (released_count for one line).
 template <bool CH>
-__device__ __forceinline__ bool released_one(const DevNet &d, const WRange &r, uint32_t o, uint32_t dv0, uint32_t dv1,
+__device__ __forceinline__ bool released_one(const DevNet &d, WRange &r, uint32_t o, uint32_t dv0, uint32_t dv1,
                                              const uint32_t *deliv) {
     const uint32_t oo = CH ? 0u : o;
     bool ok = ((r.np < 1u) | (dv0 > r.pb0 + oo)) & ((r.np < 2u) | (dv1 > r.pb1 + oo));
     if (ok & (r.np > 2u)) {
-        for (int idx = r.pd0 + 2; idx < r.pd0 + (int)r.np; idx++)
-            ok = ok & (deliv[d.pd_dix[idx]] > d.pd_base[idx] + oo);
-        vm_drain();
+        if (r.lim <= o) read_lim<CH>(d, r, deliv);
+        ok = r.lim > o;
     }
     return ok;
 }
@@ -1335,7 +1347,7 @@ __global__ void __launch_bounds__(64 * kWaveMaxWpb) engine_wave(DevNet d) {
             const uint32_t tgw = fw ? (uint32_t)gl0 + (lb & 63u) : 64u + (uint32_t)w;
             const uint32_t fkey = (hx & ~0x7Fu) | ((lb >> 6) << 5) | 1u;
             atomicMin(&word[tgw], fkey);
-            const bool sw = live & (R < rend) & released_one<CH>(d, cur, o, dv0, dv1, deliv);
+            const bool sw = live & (R < rend) && released_one<CH>(d, cur, o, dv0, dv1, deliv);
             const uint32_t skey = ((cur.start + o) << kXs) | (cur.lf << 5) | 1u;
             atomicMin(&word[sw ? (uint32_t)w : 64u + (uint32_t)w], skey);
             uint32_t nxt = (live & (occ != 0u) & (hr > t)) ? hr : kNever;
