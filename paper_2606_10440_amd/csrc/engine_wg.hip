@@ -51,6 +51,7 @@ constexpr int kC = 4;
 // kE at a time.
 constexpr int kW = 4;
 constexpr int kE = 8;
+constexpr uint32_t kR = 8;                  // request keys read at a time when ranking
 constexpr uint32_t kNoSpill = 0xFFFFFFFFu;  // a spill-list entry that holds no chunk
 
 // SM: the per-link and per-stream scalars (queue pointers, request and grant
@@ -451,8 +452,17 @@ __global__ void __launch_bounds__(kThreads, 4) engine_wg(DevNet d) {
                 const uint64_t *rec = req_rec + d.req_off[f];
                 const uint64_t ri = rec[rq.y];
                 const uint32_t ki = (uint32_t)(ri >> 32);
+                // the keys (high words) of the target's requests, kR at a time so
+                // that their loads are in flight together
+                const uint32_t *keys = reinterpret_cast<const uint32_t *>(rec) + 1;
                 int rank = 0;
-                for (uint32_t jj = 0; jj < c; jj++) rank += ((uint32_t)(rec[jj] >> 32) < ki) ? 1 : 0;
+                for (uint32_t j0 = 0; j0 < c; j0 += kR) {
+                    uint32_t kj[kR];
+#pragma unroll
+                    for (uint32_t u = 0; u < kR; u++) kj[u] = keys[2 * (size_t)(j0 + u < c ? j0 + u : c - 1)];
+#pragma unroll
+                    for (uint32_t u = 0; u < kR; u++) rank += (j0 + u < c && kj[u] < ki) ? 1 : 0;
+                }
                 const int occ = (int)(qtail[f] - (cred ? qcred[f] : qhead[f]));
                 int g = bw[f];
                 if (cap[f] - occ < g) g = cap[f] - occ;
