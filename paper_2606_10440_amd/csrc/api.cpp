@@ -83,9 +83,12 @@ struct sim_ctx {
     std::vector<int32_t> h_src, h_dst, h_step;
 
     DevNet dn{};
+    DevNet dn_lds{};                 // dn with the rings in LDS (has_lds_form)
+    bool has_lds_form = false;
     std::vector<void *> dev_static;  // freed on reload / destroy
     std::vector<void *> dev_state;
     StateLayout state;               // the engines' scratch, bound to dev_state's block in dn
+    StateLayout state_lds;           // dn_lds's scratch
     // where the last run's statuses and cycle counts are (its scratch block)
     int32_t *run_status = nullptr;
     uint64_t *run_cycles = nullptr;
@@ -800,11 +803,12 @@ sim_status finish_load(sim_ctx *c, Ranges &R) {
     const bool any_preds = !pd_flow.empty();
 
     // Engine choice.  Wave engine for small graphs batched many to a
-    // wavefront; lane engine with FIFO rings in LDS when a scenario fits a
-    // workgroup's LDS; the compact b = 1 engine for large single-line-rate
-    // graphs; the lane engine with FIFO rings in HBM when only its mailboxes
-    // fit; else the workgroup engine, resident in LDS when its per-scenario
-    // state fits.  One large topology goes to the grid engine when its
+    // wavefront; route engine for round-robin graphs of up to 1024 links; the
+    // compact engine where every link moves one line per cycle; the lane
+    // engine for the other graphs of up to 1024 links; else the workgroup
+    // engine, resident in LDS when its per-scenario state fits.  Route and
+    // lane engine keep the FIFO rings in LDS or in device memory.  One larger
+    // topology, or one with credit delays, goes to the grid engine when its
     // one-line or windowed form applies.
     auto align16 = [](int64_t v) { return (v + 15) & ~(int64_t)15; };
     const int64_t kLds = 160 * 1024;
@@ -1211,8 +1215,9 @@ sim_status finish_load(sim_ctx *c, Ranges &R) {
                                                                   align16((int64_t)nl * 2)
                                                             : (int64_t)nl * 16) +
                              (int64_t)nl * 4;
-    int32_t b1_ring = 1;
+    int32_t b1_ring = 1, b1_lg = 0;
     for (int32_t l : fsrc) b1_ring = std::max(b1_ring, fifo_mask[l] + 1);
+    while ((1 << b1_lg) < b1_ring) b1_lg++;
     const bool b1_deliv_lds = any_preds && align16(b1_words) + (int64_t)nflows * 4 + 64 <= kLds;
     const int64_t b1_bytes = align16(align16(b1_words) + (b1_deliv_lds ? (int64_t)nflows * 4 : 0)) + 64;
     // the compact engine keeps delivered counters in LDS only (its phases wait
@@ -1479,21 +1484,32 @@ sim_status finish_load(sim_ctx *c, Ranges &R) {
     // launch with rings in LDS / device memory: route engine 122 / 138 at 512
     // scenarios, 18.0 / 16.5 at 1024 and 26.2 / 16.3 at 2048 of a smaller
     // message; lane engine 34.1 / 22.7 at 512).
-    auto all_resident = [&](int64_t lds) {
+    // Rings of more than 4 GiB are not worth their memory where LDS holds them.
+    const int64_t ring_bytes = (int64_t)c->S * lf * 16, status_bytes = (int64_t)c->S * 12 + 1024;
+    auto rings_in_lds = [&](int64_t lds) {
         const int64_t waves = (nl + 63) / 64;
-        return (int64_t)c->S <= wave_blocks * std::min<int64_t>(kLds / std::max<int64_t>(lds, 1), 16 / waves);
+        return (int64_t)c->S <= wave_blocks * std::min<int64_t>(kLds / std::max<int64_t>(lds, 1), 16 / waves) ||
+               ring_bytes > (int64_t)4 << 30;
     };
+    // The allocation-free run has a fixed scratch: an engine with rings in
+    // device memory takes the place of one that needs less scratch only where
+    // its rings fit that scratch, or where its own LDS form can run there
+    // instead (dn_lds).
+    auto fits_scratch = [&](int64_t bytes) { return bytes + status_bytes <= (int64_t)SIM_NOALLOC_SCRATCH_BYTES; };
+    const bool rthbm_first =
+        rt.hbm_ok && (rt.lds_ok || fits_scratch(ring_bytes) || (!lane_ok && (b1_usable || lanehbm_ok)));
     // One line per cycle everywhere: the compact engine with one lane per
     // thread takes half the lane engine's time per cycle (k = 4 to 8
     // fat-trees under lowest id: 1.1-1.3 against 2.0-3.2 us; a 4 x 2 torus
     // of one wave: 1.0 against 1.5 us).
-    const bool b1_first = b1_usable && nl <= 1024;
+    const bool b1_first = b1_usable && nl <= 1024 &&
+                          ((!lane_ok && !(grid_ok && gl.one)) || fits_scratch(((int64_t)c->S * nl * 16) << b1_lg));
     if (wv.ok) engine = simgpu::kEngineWave;
-    else if (rt.lds_ok && (!rt.hbm_ok || all_resident(rt.bytes_lds))) engine = simgpu::kEngineRoute;
-    else if (rt.hbm_ok) engine = simgpu::kEngineRouteHbm;
+    else if (rt.lds_ok && (!rt.hbm_ok || rings_in_lds(rt.bytes_lds))) engine = simgpu::kEngineRoute;
+    else if (rthbm_first) engine = simgpu::kEngineRouteHbm;
     else if (b1_first) engine = simgpu::kEngineB1;
-    else if (lane_ok && (!lanehbm_ok || all_resident(lay_lds.bytes))) engine = simgpu::kEngineLane;
-    else if (b1_usable) engine = simgpu::kEngineB1;
+    else if (lane_ok && (!lanehbm_ok || rings_in_lds(lay_lds.bytes))) engine = simgpu::kEngineLane;
+    else if (b1_usable && !lane_ok) engine = simgpu::kEngineB1;
     else if (lanehbm_ok) engine = simgpu::kEngineLaneHbm;
     // One large topology whose lines move one per cycle per link: the grid
     // engine's one-line form spreads it over many CUs at a lower time per
@@ -1645,8 +1661,7 @@ sim_status finish_load(sim_ctx *c, Ranges &R) {
     d.o_inl = (int32_t)((int64_t)nl * 16);
     d.o_b1ino = (int32_t)((int64_t)nl * 16 + align16((int64_t)m * 2));
     d.o_b1cnt = (int32_t)(c->arb == SIM_ARB_ROUND_ROBIN ? d.o_b1ino + align16((int64_t)nl * 2) : (int64_t)nl * 16);
-    d.b1_ring_lg = 0;
-    while ((1 << d.b1_ring_lg) < b1_ring) d.b1_ring_lg++;
+    d.b1_ring_lg = b1_lg;
     d.o_b1deliv = (int32_t)align16(b1_words);
     d.o_b1red = (int32_t)(b1_bytes - 64);
     d.lane_threads = ((nl + 63) / 64) * 64;
@@ -1656,15 +1671,18 @@ sim_status finish_load(sim_ctx *c, Ranges &R) {
     }
     d.bm = bm;
     d.lds_bytes = (int32_t)lds_bytes;
-    d.o_path = (int32_t)lay.o_path;
-    d.o_deliv = (int32_t)lay.o_deliv;
-    d.o_reqcnt = (int32_t)lay.o_reqcnt;
-    d.o_reqb = (int32_t)lay.o_reqb;
-    d.o_req = (int32_t)lay.o_req;
-    d.o_glist = (int32_t)lay.o_glist;
-    d.o_grant = (int32_t)lay.o_grant;
-    d.o_gdep = (int32_t)lay.o_gdep;
-    d.o_red = (int32_t)lay.o_red;
+    auto set_lane = [](DevNet &d, const LaneLayout &lay) {
+        d.o_path = (int32_t)lay.o_path;
+        d.o_deliv = (int32_t)lay.o_deliv;
+        d.o_reqcnt = (int32_t)lay.o_reqcnt;
+        d.o_reqb = (int32_t)lay.o_reqb;
+        d.o_req = (int32_t)lay.o_req;
+        d.o_glist = (int32_t)lay.o_glist;
+        d.o_grant = (int32_t)lay.o_grant;
+        d.o_gdep = (int32_t)lay.o_gdep;
+        d.o_red = (int32_t)lay.o_red;
+    };
+    set_lane(d, lay);
     d.wv_G = wv.G;
     d.wv_W = wv.W;
     d.wv_nblk = wv.nblk;
@@ -1898,6 +1916,7 @@ sim_status finish_load(sim_ctx *c, Ranges &R) {
     sl = StateLayout{};
     sl.add(&DevNet::status, S);
     sl.add(&DevNet::cycles, S);
+    c->state_lds = sl;
     if (engine == simgpu::kEngineLaneHbm || engine == simgpu::kEngineGrid || engine == simgpu::kEngineRouteHbm)
         sl.add(&DevNet::gfifo, S * (size_t)lf);
     if (engine == simgpu::kEngineGrid) {
@@ -1960,6 +1979,20 @@ sim_status finish_load(sim_ctx *c, Ranges &R) {
     if ((st = alloc(c, c->dev_state, sl.bytes, &block))) return st;
     sl.apply(d, block);
     c->dn = d;
+    // the form of the engine with rings in LDS, for a run whose scratch is too
+    // small for rings in device memory
+    c->dn_lds = d;
+    c->has_lds_form = true;
+    if (engine == simgpu::kEngineRouteHbm && rt.lds_ok) {
+        c->dn_lds.engine = simgpu::kEngineRoute;
+        c->dn_lds.lds_bytes = (int32_t)rt.bytes_lds;
+    } else if (engine == simgpu::kEngineLaneHbm && lane_ok) {
+        c->dn_lds.engine = simgpu::kEngineLane;
+        c->dn_lds.lds_bytes = (int32_t)lay_lds.bytes;
+        set_lane(c->dn_lds, lay_lds);
+    } else {
+        c->has_lds_form = false;
+    }
     c->loaded = true;
     c->ran = false;
     return SIM_OK;
@@ -2213,11 +2246,14 @@ sim_status run_impl(sim_ctx *c, void *stream, uint32_t *d_completion, uint64_t *
         return fail(c, SIM_ERR_DEVICE, "current HIP device differs from the context's device");
     DevNet d = c->dn;
     if (scratch) {
-        if (c->state.bytes > scratch_bytes)
-            return fail(c, SIM_ERR_SIZE, "the loaded workload needs " + std::to_string(c->state.bytes) +
+        const bool lds_form = c->state.bytes > scratch_bytes && c->has_lds_form;
+        if (lds_form) d = c->dn_lds;
+        const StateLayout &sl = lds_form ? c->state_lds : c->state;
+        if (sl.bytes > scratch_bytes)
+            return fail(c, SIM_ERR_SIZE, "the loaded workload needs " + std::to_string(sl.bytes) +
                                              " B of engine scratch, more than the " + std::to_string(scratch_bytes) +
                                              " B of the allocation-free run");
-        c->state.apply(d, scratch);
+        sl.apply(d, scratch);
     }
     d.completion = d_completion;
     d.tx_lines = d_tx_lines;

@@ -1544,7 +1544,7 @@ __global__ void __launch_bounds__(1024) engine_gridw(DevNet d) {
 // ----------------------------------------------------------------------------
 // Windowed form, one wavefront per workgroup: the same windows and exchange,
 // for workgroups of at most 64 source and 64 target sides whose lines carry
-// their remaining route in one word (gd_code; the route engine's form).
+// their remaining route in one word (rt_code; the route engine's form).
 // Nothing in a window needs a barrier: LDS operations of one wave complete in
 // issue order, so its phases are separated by compiler barriers only, and
 // the nodes are spread over up to one workgroup per compute unit, because a

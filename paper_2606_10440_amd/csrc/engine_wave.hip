@@ -23,7 +23,11 @@
 // branches in the common path: a lane with nothing to store writes to a
 // trash slot of its own instead of branching around the store.
 //
-// Two cycle loops:
+// Four kinds of cycle loop, the cheapest that a load's graph allows:
+//   chain              lined-up graphs (the links form paths) with at most one
+//                      flow on from a link and one out of it: no local flow
+//                      tables, requests and grants by wave shifts.
+//   shift              other lined-up graphs.
 //   b = 1, lowest id   every requester takes the atomic minimum of its key
 //                      (line << 7 | local flow at the target << 5 | 1) on the
 //                      target's word; the word was reset at the end of the
