@@ -861,6 +861,13 @@ __global__ void __launch_bounds__(64 * kWaveMaxWpb) engine_wave(DevNet d) {
                 processed += iters;
                 live = false;
             }
+            // Its lanes move nothing while the wave's other scenarios go on:
+            // no head is ready, and the stream has no line left.
+            hy = past ? kNever : hy;
+            R = past ? rend : R;
+            no = past ? 0u : no;
+            nlen = past ? 1u : nlen;
+            pbp = past ? 0xFFFFFFFFu : pbp;
         };
         auto slow = [&](bool idle) {
             const bool act = live & (ne | (R < rend));
@@ -1101,6 +1108,9 @@ __global__ void __launch_bounds__(64 * kWaveMaxWpb) engine_wave(DevNet d) {
                 processed += iters;
                 live = false;
             }
+            // (as in chain1: its lanes offer nothing from here on)
+            occ = past ? 0u : occ;
+            R = past ? rend : R;
         };
         auto slow = [&](bool idle) {
             const bool act = live & ((occ != 0u) | (R < rend));

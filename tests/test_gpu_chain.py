@@ -70,6 +70,37 @@ def test_max_cycles(simmod, bws, monkeypatch):
     s.close()
 
 
+@pytest.mark.parametrize("arb,coll", [(0, si.COLL_RING_ALLREDUCE), (1, si.COLL_RING_ALLREDUCE),
+                                      (0, si.COLL_RHD_ALLREDUCE)])
+@pytest.mark.parametrize("dep", [si.DEP_LINE, si.DEP_CHUNK])
+@pytest.mark.parametrize("bws", [(1,), (2,), (4,), (8,)])
+def test_stopped_by_guard(simmod, oracle_lib, bws, dep, arb, coll, monkeypatch):
+    """Scenarios of one wave that the cycle guard stops early, late and not at
+    all: each leaves exactly what the oracle leaves when stopped at the same
+    cycle, whatever the wave's other scenarios still do."""
+    monkeypatch.setenv("SIMGPU_ENGINE", "wave")
+    w = si.torus2d(4, 2, n_scenarios=12, seed=51, bws=bws, lat_lo=2, lat_hi=40, depths=(2, 5, 16), nbytes=128 * 8 * 24,
+                   arb=arb, coll=coll)
+    w.dep = dep
+    if coll == si.COLL_RHD_ALLREDUCE:
+        w.order = si.gray_torus_order(4, 2)
+    s = simmod.Simulator.from_workload(w)
+    mks = np.sort([oracle_lib.simulate_workload(w, k).makespan for k in range(w.n_scenarios)])
+    for mc in (1, int(mks[0]) // 2, int(mks[0]) + 3, int(mks[len(mks) // 2]), int(mks[-1]) - 2):
+        outs = s.alloc_outputs()
+        for o in outs:
+            o.fill_(-1)
+        r = s.run(max_cycles=mc, outs=outs)
+        for k in range(w.n_scenarios):
+            want = oracle_lib.simulate_workload(w, k, max_cycles=mc)
+            assert int(r.scenario_status[k]) == {"OK": 0, "MAX_CYCLES": 8}[want.status_name], (mc, k)
+            assert np.array_equal(r.tx_lines[k].cpu().numpy().astype(np.uint64), want.tx_lines), (mc, k)
+            assert np.array_equal(r.busy_cycles[k].cpu().numpy().astype(np.uint64), want.busy_cycles), (mc, k)
+            # (lines that did not complete keep the buffer's fill)
+            assert np.array_equal(r.completion[k].cpu().numpy().view(np.uint32), want.completion), (mc, k)
+    s.close()
+
+
 @pytest.mark.parametrize("dep", [si.DEP_LINE, si.DEP_CHUNK])
 def test_same_as_shift_loop(simmod, oracle_lib, dep, monkeypatch):
     """The same bytes and processed cycles as the shift loop."""
