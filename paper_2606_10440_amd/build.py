@@ -14,7 +14,7 @@ ROOT = os.path.dirname(HERE)
 LIB = os.path.join(HERE, "libsimgpu.so")
 CSRC = os.path.join(HERE, "csrc")
 SOURCES = ["api.cpp", "engine_launch.cpp", "engine_wg.hip", "engine_lane.hip", "engine_b1.hip",
-           "engine_wave.hip", "engine_grid.hip", "engine_res.hip", "engine_route.hip", "noalloc.hip"]
+           "engine_wave.hip", "engine_wave_rr8.hip", "engine_grid.hip", "engine_res.hip", "engine_route.hip", "noalloc.hip"]
 ARCH = os.environ.get("SIMGPU_ARCH", "gfx950")
 OBJDIR = os.path.join(ROOT, "_build", "simgpu")
 
@@ -48,9 +48,12 @@ def _run(cmd, verbose):
 # iterative-ILP / max-ILP scheduler: ring sweep 271 / 291 / 268 at one line,
 # 881 / 826 / 822 at four, per-chunk 821 / 753 / 756 at four, tree sweep
 # 1521 / 1508 / 1436 at four, and the iterative one crashes the compiler on
-# small changes; the resident and grid engines ran slower so)
+# small changes; its round-robin general loop at eight lines, 4836 / 4000 /
+# 4575, keeps the iterative one, in a source of its own; the resident and grid
+# engines ran slower so)
 EXTRA = {"engine_res.hip": ["-mllvm", "-amdgpu-atomic-optimizer-strategy=DPP"],
          "engine_wave.hip": ["-mllvm", "-amdgpu-sched-strategy=max-ilp"],
+         "engine_wave_rr8.hip": ["-mllvm", "-amdgpu-sched-strategy=iterative-ilp"],
          "engine_lane.hip": ["-mllvm", "-amdgpu-sched-strategy=max-ilp"]}
 
 

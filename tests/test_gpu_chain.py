@@ -117,3 +117,29 @@ def test_same_as_shift_loop(simmod, oracle_lib, dep, monkeypatch):
         s.close()
     assert all(np.array_equal(a, b) for a, b in zip(*got))
     assert got[0][4][0] == oracle_lib.simulate_workload(w, 0).processed_cycles
+
+
+@pytest.mark.parametrize("dep", [si.DEP_LINE, si.DEP_CHUNK])
+@pytest.mark.parametrize("bws", [(8,), (5, 8), (1, 2, 4, 8)])
+def test_general_round_robin_eight_lines(simmod, oracle_lib, bws, dep):
+    """The round-robin loops of graphs that are not lined up, at up to eight
+    lines per cycle: several feeders per link (trees), with up to four
+    predecessors per range (halving-doubling)."""
+    for coll in (si.COLL_DBT_ALLREDUCE, si.COLL_RHD_ALLREDUCE):
+        w = si.torus2d(4, 2, n_scenarios=9, seed=61, bws=bws, lat_lo=1, lat_hi=12, depths=(9, 24, 40),
+                       nbytes=128 * 16 * 7, arb=1, coll=coll)
+        w.dep = dep
+        check_engine(simmod, oracle_lib, w, "wave", must_run=True)
+
+
+@pytest.mark.parametrize("b,cap", [(8, 40), (6, 9), (8, 3)])
+def test_general_round_robin_ring_of_links(simmod, oracle_lib, b, cap):
+    """One feeder per link, on a cycle: the same loops with two request groups."""
+    rp, ci = np.array([0, 1, 2, 3], np.int32), np.array([1, 2, 0], np.int32)
+    rng = np.random.default_rng(b + cap)
+    src = rng.integers(0, 3, 90).astype(np.int32)
+    dst = ((src + rng.integers(1, 3, 90)) % 3).astype(np.int32)
+    par = np.full(3, b, np.int32)
+    w = si.Workload("ring3", 3, 3, rp, ci, 1, par, np.full(3, 2, np.int32), np.full(3, cap, np.int32), 1, -1, 0)
+    check_engine(simmod, oracle_lib, w, "wave", txns=(src, dst, np.zeros(91, np.int64), np.zeros(0, np.int64)),
+                 must_run=True)
