@@ -83,12 +83,12 @@ struct sim_ctx {
     std::vector<int32_t> h_src, h_dst, h_step;
 
     DevNet dn{};
-    DevNet dn_lds{};                 // dn with the rings in LDS (has_lds_form)
-    bool has_lds_form = false;
+    DevNet dn_alt{};                 // the load on an engine that needs less scratch (has_alt)
+    bool has_alt = false;
     std::vector<void *> dev_static;  // freed on reload / destroy
     std::vector<void *> dev_state;
     StateLayout state;               // the engines' scratch, bound to dev_state's block in dn
-    StateLayout state_lds;           // dn_lds's scratch
+    StateLayout state_alt;           // dn_alt's scratch
     // where the last run's statuses and cycle counts are (its scratch block)
     int32_t *run_status = nullptr;
     uint64_t *run_cycles = nullptr;
@@ -1485,28 +1485,31 @@ sim_status finish_load(sim_ctx *c, Ranges &R) {
     // scenarios, 18.0 / 16.5 at 1024 and 26.2 / 16.3 at 2048 of a smaller
     // message; lane engine 34.1 / 22.7 at 512).
     // Rings of more than 4 GiB are not worth their memory where LDS holds them.
-    const int64_t ring_bytes = (int64_t)c->S * lf * 16, status_bytes = (int64_t)c->S * 12 + 1024;
+    const int64_t ring_bytes = (int64_t)c->S * lf * 16, b1_ring_bytes = ((int64_t)c->S * nl * 16) << b1_lg;
+    const int64_t kMostRings = (int64_t)4 << 30;
     auto rings_in_lds = [&](int64_t lds) {
         const int64_t waves = (nl + 63) / 64;
         return (int64_t)c->S <= wave_blocks * std::min<int64_t>(kLds / std::max<int64_t>(lds, 1), 16 / waves) ||
-               ring_bytes > (int64_t)4 << 30;
+               ring_bytes > kMostRings;
     };
-    // The allocation-free run has a fixed scratch: an engine with rings in
-    // device memory takes the place of one that needs less scratch only where
-    // its rings fit that scratch, or where its own LDS form can run there
-    // instead (dn_lds).
-    auto fits_scratch = [&](int64_t bytes) { return bytes + status_bytes <= (int64_t)SIM_NOALLOC_SCRATCH_BYTES; };
-    const bool rthbm_first =
-        rt.hbm_ok && (rt.lds_ok || fits_scratch(ring_bytes) || (!lane_ok && (b1_usable || lanehbm_ok)));
     // One line per cycle everywhere: the compact engine with one lane per
-    // thread takes half the lane engine's time per cycle (k = 4 to 8
-    // fat-trees under lowest id: 1.1-1.3 against 2.0-3.2 us; a 4 x 2 torus
-    // of one wave: 1.0 against 1.5 us).
+    // thread takes less time than the lane engine with either ring placement
+    // at every batch size (ms, compact / lane in LDS / lane in device memory:
+    // k = 4 fat-trees 2.46 / 4.43 / 4.62 at 16 scenarios, 2.71 / 4.88 / 5.01 at
+    // 128, 3.04 / 15.6 / 5.70 at 1200, 3.35 / 27.0 / 6.87 at 2400; a mesh of 12,
+    // direct, 1.47 / 2.04 / 2.10 at 128 and 2.62 / 10.0 / 3.87 at 2400; 4 x 4
+    // domains behind a fabric 3.45 / 5.23 / 5.41 at 128 and 5.05 / 44.8 / 9.92
+    // at 2400).  Its rings are all as long as the longest.  One scenario that
+    // does not fit the lane engine's LDS goes to the grid engine if a few deep
+    // links among shallow ones make them too long for the allocation-free run,
+    // which the grid engine's rings still fit.
+    const int64_t kScratch = SIM_NOALLOC_SCRATCH_BYTES;
     const bool b1_first = b1_usable && nl <= 1024 &&
-                          ((!lane_ok && !(grid_ok && gl.one)) || fits_scratch(((int64_t)c->S * nl * 16) << b1_lg));
+                          (lane_ok ? b1_ring_bytes <= kMostRings
+                                   : !(grid_ok && gl.one && b1_ring_bytes + 4096 > kScratch && ring_bytes <= kScratch));
     if (wv.ok) engine = simgpu::kEngineWave;
     else if (rt.lds_ok && (!rt.hbm_ok || rings_in_lds(rt.bytes_lds))) engine = simgpu::kEngineRoute;
-    else if (rthbm_first) engine = simgpu::kEngineRouteHbm;
+    else if (rt.hbm_ok) engine = simgpu::kEngineRouteHbm;
     else if (b1_first) engine = simgpu::kEngineB1;
     else if (lane_ok && (!lanehbm_ok || rings_in_lds(lay_lds.bytes))) engine = simgpu::kEngineLane;
     else if (b1_usable && !lane_ok) engine = simgpu::kEngineB1;
@@ -1544,6 +1547,17 @@ sim_status finish_load(sim_ctx *c, Ranges &R) {
         if (want < 0 || !ok) return fail(c, SIM_ERR_INVALID_ARG, std::string("SIMGPU_ENGINE=") + ev + " is not usable here");
         engine = want;
     }
+
+    // The engine of a run that cannot have this one's rings in device memory:
+    // the same engine or the lane engine with its rings in LDS (both serve any
+    // lane order), else, where only the workgroup engine could have run, that
+    // one (12 B per ring entry).
+    int alt = -1;
+    if (engine == simgpu::kEngineRouteHbm && rt.lds_ok) alt = simgpu::kEngineRoute;
+    else if ((engine == simgpu::kEngineRouteHbm || engine == simgpu::kEngineLaneHbm || engine == simgpu::kEngineB1) && lane_ok)
+        alt = simgpu::kEngineLane;
+    else if (engine == simgpu::kEngineRouteHbm && !b1_usable && !lanehbm_ok && !res.ok)
+        alt = simgpu::kEngineWorkgroup;
 
     // Lane order: traffic links ascending; the compact engine puts the links
     // that start a stream first so that stream j is owned by thread j.
@@ -1742,7 +1756,7 @@ sim_status finish_load(sim_ctx *c, Ranges &R) {
         int32_t *tmp_credit;
         UP(c->credit, credit);
     }
-    if (engine == simgpu::kEngineWorkgroup || engine == simgpu::kEngineResident) {
+    if (engine == simgpu::kEngineWorkgroup || engine == simgpu::kEngineResident || alt == simgpu::kEngineWorkgroup) {
         // streams to wake when a flow delivers: every flow that a range of the
         // stream waits on (flow-major CSR, each stream once per flow)
         std::vector<std::pair<int32_t, int32_t>> fs;
@@ -1912,87 +1926,90 @@ sim_status finish_load(sim_ctx *c, Ranges &R) {
 #undef UP
     const size_t S = (size_t)c->S;
     const size_t nsrc = (size_t)m + (size_t)d.ns;
-    StateLayout &sl = c->state;
-    sl = StateLayout{};
-    sl.add(&DevNet::status, S);
-    sl.add(&DevNet::cycles, S);
-    c->state_lds = sl;
-    if (engine == simgpu::kEngineLaneHbm || engine == simgpu::kEngineGrid || engine == simgpu::kEngineRouteHbm)
-        sl.add(&DevNet::gfifo, S * (size_t)lf);
-    if (engine == simgpu::kEngineGrid) {
-        sl.add(&DevNet::gd_pub, 4 * (size_t)nl);
-        if (gl.one) sl.add(&DevNet::gd_tpub, 4 * (size_t)nl);
-        sl.add(&DevNet::gd_dslot, 2 * (size_t)nflows);
-        sl.add(&DevNet::gd_sync, 16);
-    }
-    if (engine == simgpu::kEngineB1) {  // uniform rings: lane i owns entries [i << lg, (i + 1) << lg)
-        d.fifo_total = nl << d.b1_ring_lg;
-        sl.add(&DevNet::gfifo, S * (size_t)d.fifo_total);
-    }
-    if (engine == simgpu::kEngineResident) {
-        sl.add(&DevNet::wr_frec, S * ftot);
-        sl.add(&DevNet::delivered, S * nflows);
-        if (res.ovf > 0) {
-            const size_t ov = S * (size_t)res.ovf;
-            sl.add(&DevNet::wr_ox, ov);
-            sl.add(&DevNet::wr_opp, ov);
-            sl.add(&DevNet::wr_okey, ov);
-            sl.add(&DevNet::wr_ots, ov);
-            sl.add(&DevNet::wr_osidx, ov);
-            sl.add(&DevNet::wr_ogl, ov);
-            sl.add(&DevNet::wr_osrc, ov);
-            sl.add(&DevNet::wr_og, ov);
-            sl.add(&DevNet::wr_osrcid, ov);
-            if (fair) sl.add(&DevNet::wr_oaux, ov);
+    // an engine's scratch
+    auto engine_state = [&](int engine) {
+        StateLayout sl;
+        sl.add(&DevNet::status, S);
+        sl.add(&DevNet::cycles, S);
+        if (engine == simgpu::kEngineLaneHbm || engine == simgpu::kEngineGrid || engine == simgpu::kEngineRouteHbm)
+            sl.add(&DevNet::gfifo, S * (size_t)lf);
+        if (engine == simgpu::kEngineGrid) {
+            sl.add(&DevNet::gd_pub, 4 * (size_t)nl);
+            if (gl.one) sl.add(&DevNet::gd_tpub, 4 * (size_t)nl);
+            sl.add(&DevNet::gd_dslot, 2 * (size_t)nflows);
+            sl.add(&DevNet::gd_sync, 16);
         }
-        if (res.tovf > 0) {
-            const size_t tv = S * (size_t)res.tovf;
-            sl.add(&DevNet::wr_otmask, tv);
-            sl.add(&DevNet::wr_otseg, tv);
-            sl.add(&DevNet::wr_otq, tv);
+        if (engine == simgpu::kEngineB1)  // uniform rings: lane i owns entries [i << lg, (i + 1) << lg)
+            sl.add(&DevNet::gfifo, S * ((size_t)nl << d.b1_ring_lg));
+        if (engine == simgpu::kEngineResident) {
+            sl.add(&DevNet::wr_frec, S * ftot);
+            sl.add(&DevNet::delivered, S * nflows);
+            if (res.ovf > 0) {
+                const size_t ov = S * (size_t)res.ovf;
+                sl.add(&DevNet::wr_ox, ov);
+                sl.add(&DevNet::wr_opp, ov);
+                sl.add(&DevNet::wr_okey, ov);
+                sl.add(&DevNet::wr_ots, ov);
+                sl.add(&DevNet::wr_osidx, ov);
+                sl.add(&DevNet::wr_ogl, ov);
+                sl.add(&DevNet::wr_osrc, ov);
+                sl.add(&DevNet::wr_og, ov);
+                sl.add(&DevNet::wr_osrcid, ov);
+                if (fair) sl.add(&DevNet::wr_oaux, ov);
+            }
+            if (res.tovf > 0) {
+                const size_t tv = S * (size_t)res.tovf;
+                sl.add(&DevNet::wr_otmask, tv);
+                sl.add(&DevNet::wr_otseg, tv);
+                sl.add(&DevNet::wr_otq, tv);
+            }
         }
-    }
-    if (engine == simgpu::kEngineWorkgroup) {
-        sl.add(&DevNet::fifo_x, S * ftot);
-        sl.add(&DevNet::fifo_rdy, S * ftot);
-        sl.add(&DevNet::fifo_pp, S * ftot);
-        sl.add(&DevNet::qhead, S * m);
-        sl.add(&DevNet::qcred, S * m);
-        sl.add(&DevNet::cptr, S * m);
-        if (fair) sl.add(&DevNet::req_aux, S * rtot);
-        sl.add(&DevNet::qtail, S * m);
-        sl.add(&DevNet::rr, S * m);
-        sl.add(&DevNet::cur_rng, S * d.ns);
-        sl.add(&DevNet::cur_off, S * d.ns);
-        sl.add(&DevNet::delivered, S * nflows);
-        sl.add(&DevNet::req_cnt, S * m);
-        sl.add(&DevNet::req_rec, S * rtot);
-        sl.add(&DevNet::sreq_x, S * nsrc * bmax);
-        sl.add(&DevNet::sreq_pp, S * nsrc * bmax);
-        sl.add(&DevNet::sreq_n, S * nsrc);
-        sl.add(&DevNet::grant, S * nsrc * bmax);
-        sl.add(&DevNet::gcount, S * m);
-        sl.add(&DevNet::glist, S * m * bmax);
-        sl.add(&DevNet::gdep, S * m * bmax);
+        if (engine == simgpu::kEngineWorkgroup) {
+            sl.add(&DevNet::fifo_x, S * ftot);
+            sl.add(&DevNet::fifo_rdy, S * ftot);
+            sl.add(&DevNet::fifo_pp, S * ftot);
+            sl.add(&DevNet::qhead, S * m);
+            sl.add(&DevNet::qcred, S * m);
+            sl.add(&DevNet::cptr, S * m);
+            if (fair) sl.add(&DevNet::req_aux, S * rtot);
+            sl.add(&DevNet::qtail, S * m);
+            sl.add(&DevNet::rr, S * m);
+            sl.add(&DevNet::cur_rng, S * d.ns);
+            sl.add(&DevNet::cur_off, S * d.ns);
+            sl.add(&DevNet::delivered, S * nflows);
+            sl.add(&DevNet::req_cnt, S * m);
+            sl.add(&DevNet::req_rec, S * rtot);
+            sl.add(&DevNet::sreq_x, S * nsrc * bmax);
+            sl.add(&DevNet::sreq_pp, S * nsrc * bmax);
+            sl.add(&DevNet::sreq_n, S * nsrc);
+            sl.add(&DevNet::grant, S * nsrc * bmax);
+            sl.add(&DevNet::gcount, S * m);
+            sl.add(&DevNet::glist, S * m * bmax);
+            sl.add(&DevNet::gdep, S * m * bmax);
+        }
+        return sl;
+    };
+    if (engine == simgpu::kEngineB1) d.fifo_total = nl << d.b1_ring_lg;
+    c->state = engine_state(engine);
+    c->has_alt = alt >= 0;
+    if (c->has_alt) {
+        c->state_alt = engine_state(alt);
+        DevNet &da = c->dn_alt;
+        da = d;
+        da.engine = alt;
+        if (alt == simgpu::kEngineRoute) {
+            da.lds_bytes = (int32_t)rt.bytes_lds;
+        } else if (alt == simgpu::kEngineLane) {
+            da.lds_bytes = (int32_t)lay_lds.bytes;
+            set_lane(da, lay_lds);
+        } else {
+            da.fifo_total = (int32_t)ftot;
+        }
     }
     unsigned char *block = nullptr;
-    if ((st = alloc(c, c->dev_state, sl.bytes, &block))) return st;
-    sl.apply(d, block);
+    if ((st = alloc(c, c->dev_state, c->state.bytes, &block))) return st;
+    c->state.apply(d, block);
     c->dn = d;
-    // the form of the engine with rings in LDS, for a run whose scratch is too
-    // small for rings in device memory
-    c->dn_lds = d;
-    c->has_lds_form = true;
-    if (engine == simgpu::kEngineRouteHbm && rt.lds_ok) {
-        c->dn_lds.engine = simgpu::kEngineRoute;
-        c->dn_lds.lds_bytes = (int32_t)rt.bytes_lds;
-    } else if (engine == simgpu::kEngineLaneHbm && lane_ok) {
-        c->dn_lds.engine = simgpu::kEngineLane;
-        c->dn_lds.lds_bytes = (int32_t)lay_lds.bytes;
-        set_lane(c->dn_lds, lay_lds);
-    } else {
-        c->has_lds_form = false;
-    }
     c->loaded = true;
     c->ran = false;
     return SIM_OK;
@@ -2246,9 +2263,9 @@ sim_status run_impl(sim_ctx *c, void *stream, uint32_t *d_completion, uint64_t *
         return fail(c, SIM_ERR_DEVICE, "current HIP device differs from the context's device");
     DevNet d = c->dn;
     if (scratch) {
-        const bool lds_form = c->state.bytes > scratch_bytes && c->has_lds_form;
-        if (lds_form) d = c->dn_lds;
-        const StateLayout &sl = lds_form ? c->state_lds : c->state;
+        const bool use_alt = c->state.bytes > scratch_bytes && c->has_alt;
+        if (use_alt) d = c->dn_alt;
+        const StateLayout &sl = use_alt ? c->state_alt : c->state;
         if (sl.bytes > scratch_bytes)
             return fail(c, SIM_ERR_SIZE, "the loaded workload needs " + std::to_string(sl.bytes) +
                                              " B of engine scratch, more than the " + std::to_string(scratch_bytes) +

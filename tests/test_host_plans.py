@@ -1,0 +1,171 @@
+"""The engine a load is given and the form it takes, on the CPU: the host
+builder (api.cpp) built host-only against a stand-in HIP header whose device
+memory is host memory, with a launcher that keeps what would have been
+launched (tests/hip_host_stub)."""
+from __future__ import annotations
+
+import ctypes as C
+import os
+import shutil
+import subprocess
+from dataclasses import replace
+
+import numpy as np
+import pytest
+
+import sim_inputs as si
+
+HERE = os.path.dirname(os.path.abspath(__file__))
+ROOT = os.path.dirname(HERE)
+ENGINE = {"workgroup": 0, "lane": 1, "lanehbm": 2, "b1": 3, "wave": 4, "grid": 5, "resident": 6, "route": 7,
+          "routehbm": 8}
+NAME = {v: k for k, v in ENGINE.items()}
+
+pytestmark = pytest.mark.skipif(shutil.which("g++") is None, reason="g++ not available")
+
+
+@pytest.fixture(scope="module")
+def stub_path(tmp_path_factory):
+    lib = tmp_path_factory.mktemp("plans") / "libsimgpu_plans.so"
+    subprocess.run(["g++", "-std=c++17", "-O1", "-fPIC", "-shared", "-I", os.path.join(HERE, "hip_host_stub"), "-I",
+                    os.path.join(ROOT, "include"), os.path.join(ROOT, "paper_2606_10440_amd", "csrc", "api.cpp"),
+                    os.path.join(HERE, "hip_host_stub", "engines_stub.cpp"), "-o", str(lib)], check=True)
+    return str(lib)
+
+
+@pytest.fixture
+def plans(stub_path, monkeypatch):
+    """The binding on the stand-in build."""
+    from paper_2606_10440_amd import sim
+    monkeypatch.setattr(sim, "LIB_PATH", stub_path)
+    monkeypatch.setattr(sim, "_lib", None)
+    monkeypatch.setenv("SIMGPU_STUB_DEVICE", "1")
+    for v in ("SIMGPU_ENGINE", "SIMGPU_STUB_ALLOC_MAX", "SIMGPU_WAVE_LOOP", "SIMGPU_GRID_WGS", "SIMGPU_GRID_WINDOW"):
+        monkeypatch.delenv(v, raising=False)
+    L = sim.lib()
+    L.stub_last.restype = C.c_int64
+    L.stub_last.argtypes = [C.c_char_p]
+    L.stub_blk_wave.restype = L.stub_wv_sc.restype = C.POINTER(C.c_int32)
+    return sim
+
+
+def last(sim, name):
+    return int(sim.lib().stub_last(name.encode()))
+
+
+def launch(sim, s, noalloc=False):
+    """What a run of s launches: the engine's name."""
+    (sim.sim_run_noalloc if noalloc else sim.sim_run)(s.ctx, 0, 1, 1, 1, 1, 0)  # (nothing is written)
+    return NAME[last(sim, "engine")]
+
+
+def sweep(w, S, bws, seed=1, cap=16):
+    r = np.random.default_rng(seed)
+    m = w.n_links
+    return replace(w, n_scenarios=S, lat=np.tile(w.lat[:m], S), bw=np.repeat(r.choice(bws, S), m).astype(np.int32),
+                   cap=np.full(S * m, cap, np.int32))
+
+
+def deep_stars():
+    """Four unconnected stars of 31 endpoints, 36 cables with deep buffers, all
+    pairs of a star: round-robin, four lines per cycle, latencies beyond 16 bits."""
+    p, stars = 31, 4  # endpoints around a switch; unconnected stars
+    E = p * stars
+    rp, ci = [0], []
+    for u in range(E):
+        ci.append(E + u // p)
+        rp.append(len(ci))
+    for q in range(stars):
+        ci += range(q * p, (q + 1) * p)
+        rp.append(len(ci))
+    m = len(ci)
+    cap = np.full(m, 16, np.int32)
+    cap[:36] = 16384
+    w = si.Workload("stars", E + stars, E, np.array(rp, np.int32), np.array(ci, np.int32), 1, np.full(m, 4, np.int32),
+                    np.full(m, 70000, np.int32), cap, 1, -1, 0)
+    src = np.repeat(np.arange(E), p - 1).astype(np.int32)
+    dst = np.concatenate([[v for v in range(u // p * p, u // p * p + p) if v != u] for u in range(E)]).astype(np.int32)
+    return w, (src, dst, np.zeros(len(src) + 1, np.int64), np.zeros(0, np.int64))
+
+
+# workload -> engine of sim_run, engine of the allocation-free run (None: refused)
+CHOICE = [
+    # lowest id, one line per cycle: the compact engine at every batch size; the
+    # lane engine in LDS where the compact engine's rings exceed the scratch
+    ("k4_low_b1_S30", lambda: sweep(si.fat_tree(4, nbytes=256, arb=0), 30, (1,)), "b1", "b1"),
+    ("k4_low_b1_S1100", lambda: sweep(si.fat_tree(4, nbytes=256, arb=0), 1100, (1,)), "b1", "lane"),
+    ("k6_low_b1_S600", lambda: sweep(si.fat_tree(6, nbytes=128, arb=0), 600, (1,), cap=64), "b1", None),
+    # several lines per cycle
+    ("k4_low_b2_S100", lambda: sweep(si.fat_tree(4, nbytes=256, arb=0), 100, (1, 2)), "lane", "lane"),
+    ("k4_low_b2_S1100", lambda: sweep(si.fat_tree(4, nbytes=256, arb=0), 1100, (1, 2)), "lanehbm", "lane"),
+    # round-robin: the route engine, rings in device memory where they do not
+    # fit LDS or more scenarios than the chip holds at once
+    ("k4_rr_b4_S100", lambda: sweep(si.fat_tree(4, nbytes=256, arb=1), 100, (1, 2, 4)), "route", "route"),
+    ("k4_rr_b4_S1700", lambda: sweep(si.fat_tree(4, nbytes=256, arb=1), 1700, (1, 2, 4)), "routehbm", "route"),
+    ("k8_rr_b4_S8", lambda: sweep(si.fat_tree(8, nbytes=128, arb=1), 8, (1, 2, 4), cap=32), "routehbm", "routehbm"),
+    ("k8_rr_b4_S64", lambda: sweep(si.fat_tree(8, nbytes=128, arb=1), 64, (1, 2, 4), cap=64), "routehbm", None),
+    # one large topology
+    ("k8_low_S1", lambda: si.fat_tree(8, nbytes=128, arb=0), "b1", "b1"),
+    ("k8_low_deep_S1", lambda: replace(si.fat_tree(8, nbytes=128, arb=0), cap=np.full(768, 4096, np.int32)), "b1", None),
+    ("k16_S1", lambda: si.fat_tree(16, nbytes=128), "grid", None),
+]
+
+
+# the workloads of the GPU tests of the allocation-free run
+@pytest.mark.parametrize("arb,bws,want", [
+    (si.ARB_ROUND_ROBIN, (1, 2, 4), {30: ("route", "route"), 1100: ("route", "route"), 1700: ("routehbm", "route")}),
+    (si.ARB_LOWEST_ID, (1, 2), {30: ("lane", "lane"), 1100: ("lanehbm", "lane"), 1700: ("lanehbm", "lane")}),
+    (si.ARB_LOWEST_ID, (1,), {30: ("b1", "b1"), 1100: ("b1", "lane"), 1700: ("b1", "lane")})])
+def test_noalloc_gpu_workloads(plans, arb, bws, want):
+    from tests.test_gpu_noalloc_rings import workload
+    for S, engines in want.items():
+        s = plans.Simulator.from_workload(workload(arb, bws, S))
+        assert (launch(plans, s), launch(plans, s, noalloc=True)) == engines, S
+        s.close()
+
+
+@pytest.mark.parametrize("case", CHOICE, ids=[c[0] for c in CHOICE])
+def test_engine_choice(plans, case):
+    """The engine of sim_run does not depend on the fixed scratch of the
+    allocation-free run, which has an engine of its own where it needs one."""
+    _, make, run, noalloc = case
+    s = plans.Simulator.from_workload(make())
+    try:
+        assert launch(plans, s) == run
+        if noalloc is None:
+            with pytest.raises(plans.SimError) as e:
+                launch(plans, s, noalloc=True)
+            assert e.value.status == plans.SIM_ERR_SIZE
+        else:
+            assert launch(plans, s, noalloc=True) == noalloc
+    finally:
+        s.close()
+
+
+def test_uneven_rings_stay_on_grid(plans):
+    """One deep link among shallow ones: the compact engine's rings, all as long
+    as the longest, exceed the scratch of the allocation-free run, the grid
+    engine's do not."""
+    w = si.fat_tree(8, nbytes=128, arb=0)
+    w.cap[5] = 4096
+    s = plans.Simulator.from_workload(w)
+    assert launch(plans, s) == launch(plans, s, noalloc=True) == "grid"
+    s.close()
+
+
+def test_noalloc_takes_what_other_engines_took(plans, monkeypatch):
+    """A route-engine load whose rings exceed the scratch runs there on the
+    workgroup engine if nothing else could have taken the load and its state,
+    12 B per ring entry, fits (latencies beyond the resident engine's 16 bits,
+    request slots beyond the lane engine's LDS)."""
+    w, txns = deep_stars()
+    s = plans.Simulator.from_workload(w)
+    s.load_transactions(*txns)
+    assert launch(plans, s) == "routehbm"
+    assert launch(plans, s, noalloc=True) == "workgroup"
+    s.close()
+    monkeypatch.setenv("SIMGPU_ENGINE", "lanehbm")
+    s = plans.Simulator.from_workload(w)
+    with pytest.raises(plans.SimError):
+        s.load_transactions(*txns)
+    s.close()
