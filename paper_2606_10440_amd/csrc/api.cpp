@@ -108,11 +108,18 @@ void free_list(std::vector<void *> &v) {
     v.clear();
 }
 
+// An allocation that failed: the error is reported by the load and not once
+// more by the next launch.
+sim_status out_of_memory(sim_ctx *c, size_t bytes) {
+    (void)hipGetLastError();
+    return fail(c, SIM_ERR_OOM, "hipMalloc failed (" + std::to_string(bytes) + " B)");
+}
+
 template <class T>
 sim_status upload(sim_ctx *c, std::vector<void *> &owner, const std::vector<T> &h, T **out) {
     size_t bytes = std::max<size_t>(h.size() * sizeof(T), 16);
     void *p = nullptr;
-    if (hipMalloc(&p, bytes) != hipSuccess) return fail(c, SIM_ERR_OOM, "hipMalloc failed");
+    if (hipMalloc(&p, bytes) != hipSuccess) return out_of_memory(c, bytes);
     owner.push_back(p);
     if (!h.empty() && hipMemcpy(p, h.data(), h.size() * sizeof(T), hipMemcpyHostToDevice) != hipSuccess)
         return fail(c, SIM_ERR_DEVICE, "hipMemcpy failed");
@@ -124,7 +131,7 @@ template <class T>
 sim_status alloc(sim_ctx *c, std::vector<void *> &owner, size_t count, T **out) {
     void *p = nullptr;
     if (hipMalloc(&p, std::max<size_t>(count * sizeof(T), 16)) != hipSuccess)
-        return fail(c, SIM_ERR_OOM, "hipMalloc failed (" + std::to_string(count * sizeof(T)) + " B)");
+        return out_of_memory(c, count * sizeof(T));
     owner.push_back(p);
     *out = static_cast<T *>(p);
     return SIM_OK;
@@ -1548,7 +1555,8 @@ sim_status finish_load(sim_ctx *c, Ranges &R) {
         engine = want;
     }
 
-    // The engine of a run that cannot have this one's rings in device memory:
+    // The engine of a run that cannot have this one's rings in device memory
+    // (the allocation-free run's scratch, or the device's memory, is too small):
     // the same engine or the lane engine with its rings in LDS (both serve any
     // lane order), else, where only the workgroup engine could have run, that
     // one (12 B per ring entry).
@@ -2007,7 +2015,14 @@ sim_status finish_load(sim_ctx *c, Ranges &R) {
         }
     }
     unsigned char *block = nullptr;
-    if ((st = alloc(c, c->dev_state, c->state.bytes, &block))) return st;
+    st = alloc(c, c->dev_state, c->state.bytes, &block);
+    if (st == SIM_ERR_OOM && c->has_alt) {  // no room for the rings: the engine that does without
+        d = c->dn_alt;
+        c->state = c->state_alt;
+        c->has_alt = false;
+        st = alloc(c, c->dev_state, c->state.bytes, &block);
+    }
+    if (st != SIM_OK) return st;
     c->state.apply(d, block);
     c->dn = d;
     c->loaded = true;

@@ -169,3 +169,32 @@ def test_noalloc_takes_what_other_engines_took(plans, monkeypatch):
     with pytest.raises(plans.SimError):
         s.load_transactions(*txns)
     s.close()
+
+
+@pytest.mark.parametrize("arb,bws,run,short", [(si.ARB_ROUND_ROBIN, (1, 2, 4), "routehbm", "route"),
+                                               (si.ARB_LOWEST_ID, (1, 2), "lanehbm", "lane"),
+                                               (si.ARB_LOWEST_ID, (1,), "b1", "lane")])
+def test_short_of_device_memory(plans, monkeypatch, arb, bws, run, short):
+    """Where the device has no room for the rings of a sweep, the load takes the
+    engine that keeps them in LDS."""
+    w = sweep(si.fat_tree(4, nbytes=256, arb=arb), 1700, bws)
+    for most, want in ((0, run), (16 << 20, short)):  # (the rings take 41.8 MB)
+        monkeypatch.setenv("SIMGPU_STUB_ALLOC_MAX", str(most))
+        s = plans.Simulator.from_workload(w)
+        assert launch(plans, s) == want
+        assert launch(plans, s, noalloc=True) == short
+        s.close()
+
+
+def test_after_a_load_out_of_memory(plans, monkeypatch):
+    """A load that finds no memory reports it, and the next load and run do not
+    see its error again."""
+    monkeypatch.setenv("SIMGPU_STUB_ALLOC_MAX", str(1 << 20))
+    w = sweep(si.fat_tree(8, nbytes=128, arb=1), 8, (1, 2, 4), cap=64)
+    ctx = plans.sim_create(w.n_nodes, w.n_endpoints, w.row_ptr, w.col_idx, 8, w.bw, w.lat, w.cap, w.arb)
+    with pytest.raises(plans.SimError) as e:
+        plans.sim_load_collective(ctx, w.coll, w.bytes)
+    assert e.value.status == plans.SIM_ERR_OOM
+    plans.sim_load_transactions(ctx, [0], [1], [0, 0], [])
+    plans.sim_run(ctx, 0, 1, 1, 1, 1, 0)
+    plans.sim_destroy(ctx)
