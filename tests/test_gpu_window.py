@@ -55,3 +55,22 @@ def test_max_cycles(simmod, monkeypatch):
     r = s.run(max_cycles=mk - 1)  # the last cycle that moves a line
     assert r.status == simmod.SIM_OK and int(r.makespan[0]) == mk
     s.close()
+
+
+@pytest.mark.parametrize("arb", [0, 1])
+@pytest.mark.parametrize("wgs", [2, 8])
+def test_max_cycles_many_sides(simmod, oracle_lib, wgs, arb, monkeypatch):
+    """More sides per workgroup than lanes (the multi-wave form, over several
+    workgroups): a run that ends at the guard's last cycle has ended."""
+    monkeypatch.setenv("SIMGPU_ENGINE", "grid")
+    monkeypatch.setenv("SIMGPU_GRID_WGS", str(wgs))
+    w = tree(8, 2, 6, 5, 9, arb, 9)
+    want = oracle_lib.simulate_workload(w)
+    s = simmod.Simulator.from_workload(w)
+    assert s.run(max_cycles=want.makespan - 2).status == simmod.SIM_ERR_MAX_CYCLES
+    for mc in (want.makespan - 1, want.makespan, 0):  # the last cycle that moves a line is makespan - 1
+        r = s.run(max_cycles=mc)
+        assert r.status == simmod.SIM_OK and int(r.makespan[0]) == want.makespan
+        assert np.array_equal(r.completion[0].cpu().numpy().view(np.uint32), want.completion)
+        assert np.array_equal(r.tx_lines[0].cpu().numpy().astype(np.uint64), want.tx_lines)
+    s.close()
