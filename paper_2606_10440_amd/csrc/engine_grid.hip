@@ -1170,7 +1170,7 @@ __global__ void __launch_bounds__(1024) engine_gridw(DevNet d) {
         const int i0 = d.gd_iptr[w], ni = d.gd_iptr[w + 1] - i0;
         for (int q = tid; q < ni; q += blockDim.x) inl[q] = d.gd_inl[i0 + q];
     }
-    if (tid < 32) red[tid] = tid == 2 ? kNever : 0u;  // [0] flags, [2] earliest offer, [3] lines completed
+    if (tid < 32) red[tid] = tid == 2 ? kNever : 0u;  // [0] flags, [2] earliest offer
     if (w == 0)
         for (int q = tid; q < m; q += blockDim.x)
             if (d.link_lane[q] < 0) {
@@ -1218,7 +1218,7 @@ __global__ void __launch_bounds__(1024) engine_gridw(DevNet d) {
     }
     __syncthreads();
 
-    uint32_t T0 = 0, maxcomp = 0, done = 0;
+    uint32_t T0 = 0, maxcomp = 0;
     uint64_t widx = 0, local_cycles = 0;
     int32_t state = d.T > 0 ? kRunRunning : kRunOk;
     uint32_t lpar = 0;  // parity of the per-wave reduction slots
@@ -1228,7 +1228,6 @@ __global__ void __launch_bounds__(1024) engine_gridw(DevNet d) {
         uint32_t t = T0;
         uint32_t offer = kNever;       // this thread's events at or after wend
         bool over = false;
-        uint32_t out = 0;              // lines completed in this window
         // ------------------------------------------------ cycles of the window
         // A cycle's departures are committed at the start of the next
         // iteration (or before the exchange): whether anything moved is
@@ -1244,7 +1243,6 @@ __global__ void __launch_bounds__(1024) engine_gridw(DevNet d) {
             if (hs && (sink_f || req_f)) {
                 bool gone = sink_f;
                 if (sink_f) {
-                    out++;
                     comp[he.x] = tD + 1;
                     maxcomp = max(maxcomp, tD + 1);
                 } else {
@@ -1409,7 +1407,6 @@ __global__ void __launch_bounds__(1024) engine_gridw(DevNet d) {
                 if (wover) atomicOr(&red[0], 2u);
                 if (v != kNever) atomicMin(&red[2], v);
             }
-            if (out) atomicAdd(&red[3], out);
         }
         __syncthreads();
         bool stuck = false;
@@ -1417,8 +1414,7 @@ __global__ void __launch_bounds__(1024) engine_gridw(DevNet d) {
             const uint32_t flags = red[0];
             const int r3 = (int)(widx % 3u);
             unsigned long long *wordg = reinterpret_cast<unsigned long long *>(d.gd_sync) + r3;
-            uint32_t *nxtw = d.gd_sync + 6 + r3, *outw = d.gd_sync + 9 + r3;
-            if (red[3]) __hip_atomic_fetch_add(outw, red[3], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            uint32_t *nxtw = d.gd_sync + 6 + r3;
             if (red[2] != kNever) __hip_atomic_fetch_min(nxtw, red[2], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             __builtin_amdgcn_s_waitcnt(0x0F70);
             const unsigned long long mine = 1ull | ((flags & 1u) ? 1ull << 32 : 0ull) | ((flags & 2u) ? 1ull << 48 : 0ull);
@@ -1432,17 +1428,14 @@ __global__ void __launch_bounds__(1024) engine_gridw(DevNet d) {
                 v = ld_dev(wordg);
             }
             red[16] = stuck ? kNever : ld_dev(nxtw);
-            red[18] = stuck ? 0u : ld_dev(outw);
             red[17] = (((v >> 32) & 0xFFFFull) ? 1u : 0u) | ((v >> 48) ? 2u : 0u);
             if (w == 0 && !stuck) {
                 const int r5 = (int)((widx + 2) % 3u);
                 st_dev(reinterpret_cast<unsigned long long *>(d.gd_sync) + r5, 0ull);
                 st_dev(d.gd_sync + 6 + r5, kNever);
-                st_dev(d.gd_sync + 9 + r5, 0u);
             }
             red[0] = 0u;
             red[2] = kNever;
-            red[3] = 0u;
         } else if (j >= 0) {
             // the counts of this window; then the new entries (with their next
             // hops) and the cycles the newly popped entries left at
@@ -1512,12 +1505,9 @@ __global__ void __launch_bounds__(1024) engine_gridw(DevNet d) {
         __syncthreads();
         const uint32_t nxt = red[16];
         const uint32_t flags = red[17];
-        done += red[18];
         widx++;
         if (red[20]) {
             state = kRunWatchdog;
-        } else if (done == (uint32_t)d.T) {  // (before the guard: a run may end at its last cycle)
-            state = kRunOk;
         } else if (flags & 2u) {
             state = kRunMaxCycles;
         } else if (!(flags & 1u)) {
@@ -1544,6 +1534,19 @@ __global__ void __launch_bounds__(1024) engine_gridw(DevNet d) {
             v = u > v ? u : v;
         }
         if ((tid & 63) == 0 && v) atomicMax(&d.makespan[0], v);
+    }
+    // A run whose last line completes at the guard's last cycle has ended, but
+    // may still have had credits to wait for: the workgroups, which all stop
+    // here, say whether they have lines left (every entry is known since the
+    // last exchange), and the last one decides.
+    if (state == kRunMaxCycles) {
+        const int left = __syncthreads_or((hs && head != tkn) || (ht && R < rend));
+        if (tid == 0) {
+            if (left) __hip_atomic_fetch_add(d.gd_sync + 9, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            __builtin_amdgcn_s_waitcnt(0x0F70);
+            const uint32_t before = __hip_atomic_fetch_add(d.gd_sync + 10, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            state = before + 1u < (uint32_t)NB ? kRunRunning : ld_dev(d.gd_sync + 9) == 0u ? kRunOk : state;
+        }
     }
     if (tid == 0) {
         atomicMax(&d.status[0], state);
