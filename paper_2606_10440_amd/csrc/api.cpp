@@ -1348,20 +1348,20 @@ sim_status finish_load(sim_ctx *c, Ranges &R) {
             gl = grid_layout(c, fsrc, has_stream, feeders, fsrc_pos, bmax, bm, nflows, pd_flow, nb, port_at_head,
                              nports);
         };
-        layout(want_nb);
-        gl.wave = win_try && code_ok && gl.one && win >= 2 && gl.ns_max <= 64 && gl.nt_max <= 64 &&
-                  !std::getenv("SIMGPU_GRID_GENERAL");
-        if (!gl.wave && want_nb > few_nb) layout(few_nb);  // the other forms run on one die
-        if (std::getenv("SIMGPU_GRID_GENERAL")) gl.one = false;  // tests: the general form on b = 1 graphs
-        if (gl.one && gl.one_bytes <= kLds) {
-            gl.bytes = gl.one_bytes;
-            gl.threads = gl.one_threads;
-        } else {
-            gl.one = gl.wave = false;
-        }
-        // Credit delays: the windowed form, when every traffic link has
-        // latency and credit delay of at least 2 and no line waits on another.
-        if (credits) {
+        const bool general = std::getenv("SIMGPU_GRID_GENERAL") != nullptr;  // tests: the general form on b = 1 graphs
+        // the kernel form of the layout and its LDS
+        auto size = [&](bool wave) {
+            gl.wave = wave;
+            if (general) gl.one = false;
+            if (gl.one && gl.one_bytes <= kLds) {
+                gl.bytes = gl.one_bytes;
+                gl.threads = gl.one_threads;
+            } else {
+                gl.one = gl.wave = false;
+            }
+            if (!credits) return;
+            // Credit delays: the windowed form, when every traffic link has
+            // latency and credit delay of at least 2 and no line waits on another.
             if (gl.one && !any_preds && win >= 2) {
                 std::vector<int32_t> ring_of(nl);
                 for (int32_t i = 0; i < nl; i++) ring_of[i] = fifo_mask[fsrc[i]] + 1;
@@ -1397,6 +1397,32 @@ sim_status finish_load(sim_ctx *c, Ranges &R) {
             } else {
                 gl.bytes = INT64_MAX;  // credit delays need the windowed form
             }
+        };
+        layout(want_nb);
+        // The one-wave form reads the new entries of eight sides at a time, one
+        // eight after the other in every window.  With short windows and more
+        // than four sides per workgroup and cycle of a window this takes longer
+        // than the cycles it saves; the multi-wave form then runs on eight
+        // workgroups, as the exchange is most of its time (ms, multi-wave on 32 /
+        // on 8 / one-wave: k = 10, 48 sides, 2.13 / 1.51 / 3.91 at windows of 2
+        // cycles, 1.51 / 1.31 / 2.18 at 6; k = 8, 24 sides, 3.33 / 2.22 / 4.24 at 2,
+        // 2.47 / 1.84 / 2.60 at 4, 2.46 / 2.01 / 2.44 at 6; k = 6, 11 sides, 3.23 /
+        // 2.24 / 3.00 at 2, 1.97 / 1.66 / 1.53 at 6; a mesh of 24, all pairs, 23
+        // sides, 0.83 / 0.68 / 1.08 at 2, 0.59 / 0.52 / 0.62 at 4, 0.52 / 0.53 /
+        // 0.47 at 6; k = 4, 3 sides, 0.61 / 0.51 / 0.48 at 3).
+        const bool wave_ok = win_try && code_ok && gl.one && win >= 2 && gl.ns_max <= 64 && gl.nt_max <= 64 && !general;
+        const bool short_win = wave_ok && win < 8 && std::max(gl.ns_max, gl.nt_max) > 4 * win;
+        bool wave = wave_ok && !short_win;
+        if (const char *ev = std::getenv("SIMGPU_GRID_WINDOW")) {  // tests: the form of windowed runs
+            if (!std::strcmp(ev, "wave")) wave = wave_ok;
+            if (!std::strcmp(ev, "multi")) wave = false;
+        }
+        if (!wave && short_win && !std::getenv("SIMGPU_GRID_WGS")) layout(8);
+        else if (!wave && want_nb > few_nb) layout(few_nb);  // the other forms run on one die
+        size(wave);
+        if (short_win && gl.bytes > kLds && gl.nb < few_nb) {  // eight workgroups' rings do not fit
+            layout(few_nb);
+            size(wave);
         }
     }
     const bool grid_ok = grid_try && gl.bytes <= kLds;

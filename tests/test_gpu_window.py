@@ -1,9 +1,10 @@
-"""Grid engine, windowed form with one wavefront per workgroup: parity with
-the CPU oracle where it can go wrong -- many workgroups and few, several
-nodes and sides per workgroup, buffers of one line (every head refused until
-its credit is back), batches of more entries than one read takes, windows
+"""Grid engine, windowed forms (one wavefront per workgroup, and several):
+parity with the CPU oracle where they can go wrong -- many workgroups and few,
+several nodes and sides per workgroup, buffers of one line (every head refused
+until its credit is back), batches of more entries than one read takes, windows
 shorter and longer than a buffer's drain, both arbitrations, deadlocks, the
-cycle guard at its last cycle."""
+cycle guard at its last cycle.  Which form a load takes by itself is checked in
+tests/test_host_plans.py."""
 from __future__ import annotations
 
 import numpy as np
@@ -74,3 +75,49 @@ def test_max_cycles_many_sides(simmod, oracle_lib, wgs, arb, monkeypatch):
         assert np.array_equal(r.completion[0].cpu().numpy().view(np.uint32), want.completion)
         assert np.array_equal(r.tx_lines[0].cpu().numpy().astype(np.uint64), want.tx_lines)
     s.close()
+
+
+# The multi-wave form, which short windows with many sides per workgroup take,
+# over two and more workgroups.
+
+def multi(monkeypatch, wgs=None):
+    monkeypatch.setenv("SIMGPU_GRID_WINDOW", "multi")
+    if wgs:
+        monkeypatch.setenv("SIMGPU_GRID_WGS", str(wgs))
+
+
+@pytest.mark.parametrize("arb", [0, 1])
+@pytest.mark.parametrize("k,lines,cap,lo,hi", [(4, 6, 1, 32, 40), (4, 40, 100, 64, 90), (6, 3, 7, 2, 5), (8, 2, 32, 3, 7),
+                                               (4, 5, 3, 2, 6)])
+def test_fat_tree_multi(simmod, oracle_lib, k, lines, cap, lo, hi, arb, monkeypatch):
+    multi(monkeypatch)
+    assert check_engine(simmod, oracle_lib, tree(k, lines, cap, lo, hi, arb, 80 + k), "grid", must_run=True) == 1
+
+
+@pytest.mark.parametrize("arb", [0, 1])
+@pytest.mark.parametrize("wgs", [2, 7, 32])
+def test_workgroups_multi(simmod, oracle_lib, wgs, arb, monkeypatch):
+    multi(monkeypatch, wgs)
+    assert check_engine(simmod, oracle_lib, tree(4, 8, 9, 6, 50, arb, 5), "grid", must_run=True) == 1
+
+
+@pytest.mark.parametrize("cap", [2, 4, 40])
+def test_deadlock_or_end_multi(simmod, oracle_lib, cap, monkeypatch):
+    multi(monkeypatch, 7)
+    w = si.torus2d(4, 4, n_scenarios=1, seed=3, bws=(1, 1), lat_lo=5, lat_hi=9, depths=(cap,), nbytes=128 * 24,
+                   coll=si.COLL_ALLTOALL, arb=1)
+    w.credit = (w.lat + 3).astype(np.int32)
+    check_engine(simmod, oracle_lib, w, "grid", must_run=True)
+
+
+def test_max_cycles_multi(simmod, monkeypatch):
+    multi(monkeypatch, 8)
+    test_max_cycles(simmod, monkeypatch)
+
+
+@pytest.mark.parametrize("arb", [0, 1])
+@pytest.mark.parametrize("lo", [2, 3, 4, 6, 8])
+def test_short_windows(simmod, oracle_lib, lo, arb):
+    """The form that the load takes by itself, on both sides of the rule."""
+    for k in (4, 8):
+        assert check_engine(simmod, oracle_lib, tree(k, 2, 5, lo, lo + 3, arb, 90 + lo), "grid", must_run=True) == 1

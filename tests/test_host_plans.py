@@ -198,3 +198,41 @@ def test_after_a_load_out_of_memory(plans, monkeypatch):
     plans.sim_load_transactions(ctx, [0], [1], [0, 0], [])
     plans.sim_run(ctx, 0, 1, 1, 1, 1, 0)
     plans.sim_destroy(ctx)
+
+
+# (tree size, shortest latency and credit delay) -> one wave per workgroup?, workgroups
+@pytest.mark.parametrize("k,lo,wave,nb", [(4, 2, True, 32), (4, 64, True, 32), (6, 2, False, 8), (6, 3, True, 32),
+                                          (6, 8, True, 99), (8, 2, False, 8), (8, 5, False, 8), (8, 8, True, 208)])
+def test_windowed_form(plans, k, lo, wave, nb):
+    """Short windows with many sides per workgroup take the multi-wave form."""
+    w = si.fat_tree(k, nbytes=128, lat_lo=lo, lat_hi=lo + 3)
+    w.credit = np.maximum(w.lat, lo).astype(np.int32)
+    w.lat[0] = w.credit[0] = lo
+    s = plans.Simulator.from_workload(w)
+    assert launch(plans, s) == "grid"
+    assert last(plans, "gd_window") == lo
+    assert (bool(last(plans, "gd_wave")), last(plans, "gd_nb")) == (wave, nb)
+    s.close()
+
+
+def test_windowed_form_deep_buffers(plans):
+    """Eight workgroups' rings beyond LDS: the multi-wave form on 32."""
+    w = si.fat_tree(8, nbytes=128, lat_lo=3, lat_hi=5, cap=128)
+    w.credit = w.lat.copy()
+    s = plans.Simulator.from_workload(w)
+    assert launch(plans, s) == "grid"
+    assert (last(plans, "gd_wave"), last(plans, "gd_nb")) == (0, 32) and last(plans, "lds_bytes") <= 160 * 1024
+    s.close()
+
+
+def test_windowed_form_gpu_workloads(plans, monkeypatch):
+    """The forms that tests/test_gpu_window.py means to run."""
+    from tests.test_gpu_window import tree
+    for env, want in ({}, 1), ({"SIMGPU_GRID_WINDOW": "multi"}, 0), ({"SIMGPU_GRID_WGS": "1"}, 0), ({"SIMGPU_GRID_WGS": "7"}, 1):
+        for v in ("SIMGPU_GRID_WINDOW", "SIMGPU_GRID_WGS"):
+            monkeypatch.delenv(v, raising=False)
+        for v, x in env.items():
+            monkeypatch.setenv(v, x)
+        s = plans.Simulator.from_workload(tree(4, 8, 9, 33, 50, 1, 5))
+        assert launch(plans, s) == "grid" and last(plans, "gd_wave") == want, env
+        s.close()
