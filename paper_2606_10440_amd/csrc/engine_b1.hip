@@ -98,10 +98,62 @@ __global__ void __launch_bounds__(1024) engine_b1(DevNet d) {
     uint32_t o = 0;
     RangeReg<PC> cur{};
     const bool has_stream = tid < d.b1_ns;
+    // One lane per thread, ranges with more descriptors than are cached (the
+    // others are in device memory): the lines known to be released (lim) and
+    // the predecessor that held back the next one, which is looked at first;
+    // every other one is read, eight at a time, only when that one lets go.
+    // (Direct all-reduce of 100 lines per pair on a mesh of 32, 31 predecessors:
+    // 5.09 ms with a test of one descriptor after the other in every cycle,
+    // 1.18 so; ranges with few are up to 8 % faster without.)
+    constexpr bool kHeld = LPT == 1 && PC > 0;
+    uint32_t lim = 0, hf = 0, hb = 0;
+    auto new_range = [&]() {
+        load_range(d, R, cur);
+        if constexpr (kHeld) {
+            lim = 0u;
+            hf = (uint32_t)cur.pf[0];
+            hb = cur.pb[0];
+        }
+    };
+    auto may_leave = [&]() -> bool {
+        if constexpr (kHeld) {
+            if (cur.pd1 - cur.pd0 <= PC) return released(d, cur, o, deliv);
+            if (lim > o) return true;
+            const bool whole = d.pd_omask == 0u;
+            auto allow = [&](uint32_t v, uint32_t base) -> uint32_t {
+                return v > base ? (whole ? 0xFFFFFFFFu : v - base) : 0u;
+            };
+            if (allow(deliv[hf], hb) <= o) return false;
+            uint32_t a = 0xFFFFFFFFu;
+            auto look = [&](uint32_t f, uint32_t base, bool in) {
+                const uint32_t v = in ? allow(deliv[f], base) : 0xFFFFFFFFu;
+                hf = v < a ? f : hf;
+                hb = v < a ? base : hb;
+                a = v < a ? v : a;
+            };
+#pragma unroll
+            for (int q = 0; q < PC; q++) look((uint32_t)cur.pf[q], cur.pb[q], true);
+            for (int i0 = cur.pd0 + PC; i0 < cur.pd1; i0 += 8) {
+                uint32_t f[8], bs[8];
+#pragma unroll
+                for (int q = 0; q < 8; q++) {
+                    const int idx = i0 + q < cur.pd1 ? i0 + q : i0;
+                    f[q] = (uint32_t)d.pd_flow[idx];
+                    bs[q] = d.pd_base[idx];
+                }
+#pragma unroll
+                for (int q = 0; q < 8; q++) look(f[q], bs[q], i0 + q < cur.pd1);
+            }
+            lim = a;
+            return lim > o;
+        } else {
+            return released(d, cur, o, deliv);
+        }
+    };
     if (has_stream) {
         R = d.ln_srbeg[tid];
         rend = d.ln_srend[tid];
-        if (R < rend) load_range(d, R, cur);
+        if (R < rend) new_range();
     }
     lds_fence_block();
 
@@ -169,7 +221,7 @@ __global__ void __launch_bounds__(1024) engine_b1(DevNet d) {
         }
         bool sreq = false;
         uint32_t sx = 0;
-        if (has_stream && R < rend && released(d, cur, o, deliv)) {
+        if (has_stream && R < rend && may_leave()) {
             sreq = true;
             sx = cur.start + o;
             if (ARB == 1)
@@ -280,7 +332,7 @@ __global__ void __launch_bounds__(1024) engine_b1(DevNet d) {
                 if (++o >= cur.len) {
                     o = 0;
                     R++;
-                    if (R < rend) load_range(d, R, cur);
+                    if (R < rend) new_range();
                 }
             }
         }
