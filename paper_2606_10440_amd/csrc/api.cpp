@@ -1045,7 +1045,9 @@ sim_status finish_load(sim_ctx *c, Ranges &R) {
             // scenario's processed cycles (lines on the busiest link per cycle
             // of bandwidth, plus a few fill/drain cycles per buffer's worth of
             // lines) times the relative cost of a cycle of the loop it runs
-            // (the b = 1 loop, or the general loop unrolled to 1, 2, 4, 8).
+            // (a chain loop, the shift loop -- also under round-robin with several
+            // lines per cycle --, the b = 1 loop, or the general loop unrolled to
+            // 1, 2, 4, 8).
             std::vector<double> wtime(W, 0.0);
             for (int32_t q = 0; q < W; q++) {
                 double cyc = 0.0;
@@ -1060,7 +1062,8 @@ sim_status finish_load(sim_ctx *c, Ranges &R) {
                     }
                 }
                 const bool fast = c->arb == SIM_ARB_LOWEST_ID && wbmax == 1;
-                const double per = wv.chain ? (wbmax <= 1 ? 0.27 : wbmax <= 2 ? 0.5 : wbmax <= 4 ? 0.82 : 1.6)
+                const bool chain = wv.chain && (c->arb == SIM_ARB_LOWEST_ID || wbmax <= 1);
+                const double per = chain ? (wbmax <= 1 ? 0.27 : wbmax <= 2 ? 0.5 : wbmax <= 4 ? 0.82 : 1.6)
                                    : wv.lineup ? (wbmax <= 1 ? 0.5 : wbmax <= 2 ? 0.8 : wbmax <= 4 ? 1.2 : 2.0)
                                    : fast ? 1.0 : wbmax <= 1 ? 1.5 : wbmax <= 2 ? 1.8 : wbmax <= 4 ? 2.9 : 5.5;
                 wtime[q] = cyc * per;

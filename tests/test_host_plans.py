@@ -236,3 +236,34 @@ def test_windowed_form_gpu_workloads(plans, monkeypatch):
         s = plans.Simulator.from_workload(tree(4, 8, 9, 33, 50, 1, 5))
         assert launch(plans, s) == "grid" and last(plans, "gd_wave") == want, env
         s.close()
+
+
+@pytest.mark.parametrize("arb", [si.ARB_LOWEST_ID, si.ARB_ROUND_ROBIN])
+def test_wave_placement_costs(plans, arb):
+    """More waves than SIMDs: the shortest by the cost of the loop they run share
+    a SIMD (positions j and j + 4 of a workgroup), the longest run alone.  Under
+    round-robin, waves of several lines per cycle run the shift loop, not the
+    chain loop."""
+    S = 4500
+    w = si.torus2d(4, 4, n_scenarios=S, seed=12, bws=(1, 4), depths=(8, 12, 16, 24, 32, 48, 64), nbytes=128 * 16 * 8,
+                   arb=arb)
+    s = plans.Simulator.from_workload(w)
+    assert launch(plans, s) == "wave" and last(plans, "wv_chain") == 1
+    bw, cap = w.bw[::w.n_links], w.cap[::w.n_links].astype(float)
+    per = np.where(bw == 1, 0.27, 0.82 if arb == si.ARB_LOWEST_ID else 1.2)
+    cost = (1.0 / bw + 4.0 / cap) * per  # (lines on the busiest link: the same in every scenario)
+    nblk, wpb, W, G = (last(plans, "wv_" + v) for v in ("nblk", "wpb", "W", "G"))
+    blk = np.ctypeslib.as_array(plans.lib().stub_blk_wave(), (nblk, wpb))
+    sc = np.ctypeslib.as_array(plans.lib().stub_wv_sc(), (W * G,)).reshape(W, G)
+    assert 4 < wpb <= 8 and 1024 < W <= 2048
+    wave = np.array([cost[v[v >= 0]].max() for v in sc])  # as long as its longest scenario
+    alone, shared = [], []
+    for b in blk:
+        for j in range(4):
+            if b[j] < 0:
+                continue
+            pair = [b[j]] + [b[q] for q in (j + 4,) if q < wpb and b[q] >= 0]
+            (shared if len(pair) == 2 else alone).extend(pair)
+    assert sorted(alone + shared) == list(range(W))
+    assert wave[alone].min() >= wave[shared].max() - 1e-9
+    s.close()
