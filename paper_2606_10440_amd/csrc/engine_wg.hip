@@ -454,12 +454,11 @@ __global__ void __launch_bounds__(kThreads, 4) engine_wg(DevNet d) {
                 const uint32_t ki = (uint32_t)(ri >> 32);
                 // the keys (high words) of the target's requests, kR at a time so
                 // that their loads are in flight together
-                const uint32_t *keys = reinterpret_cast<const uint32_t *>(rec) + 1;
                 int rank = 0;
                 for (uint32_t j0 = 0; j0 < c; j0 += kR) {
                     uint32_t kj[kR];
 #pragma unroll
-                    for (uint32_t u = 0; u < kR; u++) kj[u] = keys[2 * (size_t)(j0 + u < c ? j0 + u : c - 1)];
+                    for (uint32_t u = 0; u < kR; u++) kj[u] = (uint32_t)(rec[j0 + u < c ? j0 + u : c - 1] >> 32);
 #pragma unroll
                     for (uint32_t u = 0; u < kR; u++) rank += (j0 + u < c && kj[u] < ki) ? 1 : 0;
                 }
