@@ -1833,6 +1833,8 @@ __global__ void __launch_bounds__(64) engine_gridv(DevNet d) {
         if (!stuck) {
             const uint32_t ncs = hs ? ntail - tkn : 0u, nct = ht ? npk - pk : 0u;
             const int most = ns > nt ? ns : nt;
+            // (read where every lane is active: under a branch, a copy of the value
+            // that the compiler makes there would miss the other lanes)
             auto lane_of = [](uint32_t v, int q) { return (uint32_t)__builtin_amdgcn_readlane((int)v, q); };
             for (int g0 = 0; g0 < most; g0 += 8) {
                 uint32_t cmax = 0;
@@ -1846,22 +1848,22 @@ __global__ void __launch_bounds__(64) engine_gridv(DevNet d) {
 #pragma unroll
                     for (int u = 0; u < 8; u++) {
                         const int z = (g0 + u) & 63;
-                        if (q < lane_of(ncs, z)) {
-                            const size_t at = (size_t)(lane_of(s_fb, z) + ((lane_of(tkn, z) + q) & lane_of(s_fm, z)));
-                            unsigned long long *e = reinterpret_cast<unsigned long long *>(ring + 4 * at);
+                        const uint32_t cs = lane_of(ncs, z), sa = lane_of(s_fb, z) + ((lane_of(tkn, z) + q) & lane_of(s_fm, z));
+                        const uint32_t ct = lane_of(nct, z), ta = lane_of(t_fb, z) + ((lane_of(pk, z) + q) & lane_of(t_fm, z));
+                        if (q < cs) {
+                            unsigned long long *e = reinterpret_cast<unsigned long long *>(ring + 4 * (size_t)sa);
                             ex[u] = ld_dev(e);
                             er[u] = ld_dev(reinterpret_cast<uint32_t *>(e + 1));
                         }
-                        if (q < lane_of(nct, z))
-                            dc[u] = ld_dev(ring + 4 * (size_t)(lane_of(t_fb, z) + ((lane_of(pk, z) + q) & lane_of(t_fm, z))) + 3);
+                        if (q < ct) dc[u] = ld_dev(ring + 4 * (size_t)ta + 3);
                     }
 #pragma unroll
                     for (int u = 0; u < 8; u++) {
                         const int z = (g0 + u) & 63;
-                        if (q < lane_of(ncs, z))
-                            sring[lane_of(s_lo, z) + ((lane_of(tkn, z) + q) & lane_of(s_fm, z))] =
-                                make_uint4((uint32_t)ex[u], (uint32_t)(ex[u] >> 32), er[u], 0u);
-                        if (q < lane_of(nct, z)) cring[lane_of(t_co, z) + ((lane_of(pk, z) + q) & lane_of(t_fm, z))] = dc[u];
+                        const uint32_t cs = lane_of(ncs, z), sa = lane_of(s_lo, z) + ((lane_of(tkn, z) + q) & lane_of(s_fm, z));
+                        const uint32_t ct = lane_of(nct, z), ta = lane_of(t_co, z) + ((lane_of(pk, z) + q) & lane_of(t_fm, z));
+                        if (q < cs) sring[sa] = make_uint4((uint32_t)ex[u], (uint32_t)(ex[u] >> 32), er[u], 0u);
+                        if (q < ct) cring[ta] = dc[u];
                     }
                 }
             }
