@@ -1935,19 +1935,23 @@ sim_status finish_load(sim_ctx *c, Ranges &R) {
         for (int q = 0; q < 8; q++) d.rt_off[q] = (int32_t)rt.off[q];
         d.rt_zero = rt.zero;
         d.rt_np = rt.np;
-        int32_t *tmp_rt_pslot, *tmp_rt_tin, *tmp_rt_obase;
-        UP(rt_pslot, rt_pslot);
-        UP(rt_tin, rt_tin);
-        UP(rt_obase, rt_obase);
+        // (one table: a load's time is mostly its allocations and copies)
+        std::vector<int32_t> rt_tab(rt_pslot);
+        rt_tab.insert(rt_tab.end(), rt_tin.begin(), rt_tin.end());
+        rt_tab.insert(rt_tab.end(), rt_obase.begin(), rt_obase.end());
+        int32_t *tmp_rt_pslot;
+        UP(rt_tab, rt_pslot);
+        d.rt_tin = d.rt_pslot + nl;
+        d.rt_obase = d.rt_pslot + 2 * (size_t)nl;
     }
     if (engine == simgpu::kEngineWave) {
         uint32_t *tmp_wv_lfb, *tmp_wv_lfx, *tmp_wv_duo;
-        if (wv_duo.empty()) wv_duo.push_back(0);
-        UP(wv_duo, wv_duo);
-        uint32_t *tmp_wv_fmask;
-        int32_t *tmp_wv_ej;
-        UP(wv_fmask, wv_fmask);
-        UP(wv_ej, wv_ej);
+        std::vector<uint32_t> wv_tab(wv_duo);  // (one table, as above)
+        wv_tab.insert(wv_tab.end(), wv_fmask.begin(), wv_fmask.end());
+        wv_tab.insert(wv_tab.end(), wv_ej.begin(), wv_ej.end());
+        UP(wv_tab, wv_duo);
+        d.wv_fmask = d.wv_duo + nl;
+        d.wv_ej = reinterpret_cast<const int32_t *>(d.wv_duo + 2 * (size_t)nl);
         int32_t *tmp_wv_feed, *tmp_wv_nfeed, *tmp_wv_sc, *tmp_r_lf, *tmp_pd_dix;
         UP(wv_lfb, wv_lfb);
         UP(wv_lfx, wv_lfx);
