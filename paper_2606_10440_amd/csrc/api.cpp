@@ -1337,8 +1337,10 @@ sim_status finish_load(sim_ctx *c, Ranges &R) {
         // exchange over all dies take one workgroup per compute unit, shorter
         // ones and graphs of about 32 nodes one die's (k = 8 fat-tree, 208
         // nodes, ms with 32 / 256 workgroups: 12.4 / 15.1 at windows of 2
-        // cycles, 6.3 / 5.3 at 8, 10.7 / 8.2 at 32, 15.9 / 11.4 at 64; k = 4,
-        // 36 nodes: 2.43 / 2.55 at 64).
+        // cycles, 6.3 / 5.3 at 8, 10.7 / 8.2 at 32, 15.9 / 11.4 at 64; k = 6, 99
+        // nodes: 2.14 / 2.23 at 3, 1.42 / 1.28 at 8, 4.23 / 3.39 at 100; 8 x 8
+        // domains behind a fabric, 76 nodes: 7.27 / 6.97 at 2, 3.32 / 2.84 at 8,
+        // 6.95 / 6.49 at 60; k = 4, 36 nodes: 2.43 / 2.55 at 64).
         int32_t win = 0;
         if (credits) {
             win = INT32_MAX;
@@ -1519,7 +1521,10 @@ sim_status finish_load(sim_ctx *c, Ranges &R) {
     // holds more workgroups per compute unit (a k = 4 fat-tree sweep, ms per
     // launch with rings in LDS / device memory: route engine 122 / 138 at 512
     // scenarios, 18.0 / 16.5 at 1024 and 26.2 / 16.3 at 2048 of a smaller
-    // message; lane engine 34.1 / 22.7 at 512).
+    // message, lane engine 34.1 / 22.7 at 512; 4 x 4 domains behind a fabric,
+    // route 2.57 / 2.97 at 64 and 4.56 / 3.23 at 600, lane 6.40 / 6.46 at 64 and
+    // 15.2 / 6.80 at 600; a mesh of 12, route 2.25 / 2.22 at 64 and 4.33 / 2.38 at
+    // 1200, lane 3.09 / 3.21 at 64 and 7.88 / 3.76 at 1200).
     // Rings of more than 4 GiB are not worth their memory where LDS holds them.
     const int64_t ring_bytes = (int64_t)c->S * lf * 16, b1_ring_bytes = ((int64_t)c->S * nl * 16) << b1_lg;
     const int64_t kMostRings = (int64_t)4 << 30;

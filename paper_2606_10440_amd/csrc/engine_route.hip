@@ -35,6 +35,12 @@
 //   k = 8 fat-tree all-to-all, 768 links        0.88 us  (grid engine 3.07)
 //   k = 4, 512 scenarios, b in {1, 2, 4}        2.2 us   (lane engine 7.3)
 //   8 x 8 hierarchical all-reduce, 640 links    1.96 us  (lane engine 3.78)
+// Rings in device memory with predecessors and four lines (engine_route<4,
+// true, true>): the loop needs more than the 128 registers of 16 waves per
+// compute unit, and keeps 8 vector registers in scratch.  With two cached
+// descriptors instead of eight it keeps none: k = 4 fat-tree trees 6.4 -> 5.1
+// ms, but all-pairs exchanges on meshes of 9 to 20, whose ranges wait on 8 to
+// 19 flows, take 1 to 8 % longer; a rule between the two is not made yet.
 // Picking and reading every granted post before the first append (instead of
 // one after the other under a branch) made the last two 8-10 % slower: most
 // cycles grant one line per link.

@@ -773,19 +773,22 @@ __global__ void __launch_bounds__(64 * kWaveMaxWpb) engine_wave(DevNet d) {
     // id with bit 0 = the line goes on, so that "no line" is 0, the lowest id
     // is the largest word, and a word from the lane below becomes this lane's
     // by one AND with a lane constant (no feeder: 0; its lines leave here:
-    // all but bit 0).  What a lane of the wave decides about its neighbour --
-    // the line was taken -- is a bit of a wave mask shifted by one lane.
+    // all but bit 0).  A lane offers its head's word to the lane above and is
+    // handed back the word taken there, or 0, both by a DPP wave shift; a
+    // maximum decides between the feeder's word and the stream's, a minimum
+    // with the free slots whether it is appended, so most of a cycle is selects
+    // on words in vector registers.
     // The entry behind the head is read as a cycle begins and the next cycle's
     // delivered count right after the completions, so no LDS round trip is
-    // waited for; decisions are wave masks in scalar registers.  The common cycle checks
-    // only that every live scenario moved a line; a scenario that did not
-    // jumps, ends (its lines were all gone one cycle before) or deadlocks in
-    // slow().  MP: some range waits on more than one flow; then the one that
-    // held the stream back last is polled, and all are read when it lets go.
+    // waited for.  The common cycle checks only that every live scenario moved
+    // a line (a wave mask); a scenario that did not jumps, ends (its lines were
+    // all gone one cycle before) or deadlocks in slow().  MP: some range waits
+    // on more than one flow; then the one that held the stream back last is
+    // polled, and all are read when it lets go.
     // Bound: the instructions of one cycle (a lone wave issues one per four
-    // clocks).  Per cycle of a lone wave: 88 instructions and 235 ns on a mesh
-    // of 8 (434 ns in the loop above), 288 ns on the ring all-reduce sweep
-    // (178 instructions, 465 ns).
+    // clocks), 90 of them against 178 in the shift loop.  Per cycle of a lone
+    // wave: 210 ns on a mesh of 8 (shift loop: 420 ns), 235 ns on a ring
+    // all-reduce over a 4 x 4 torus (426 ns).
     auto chain1 = [&](auto mp_tag) {
         constexpr bool MP = decltype(mp_tag)::value;
         typedef __attribute__((address_space(3))) uint32_t *L32;
@@ -1034,9 +1037,9 @@ __global__ void __launch_bounds__(64 * kWaveMaxWpb) engine_wave(DevNet d) {
     // The feeder's lines and the stream's arrive as two descending lists of
     // words; a bitonic merge gives the first BMW of both in order, the smallest
     // word appended tells how many of the feeder's lines it took (those at or
-    // above it), and one shift hands that number back.  Ring all-reduce sweep,
-    // ns per cycle of a lone wave: 500 at two lines (725 in the shift loop),
-    // 830 at four (1275).
+    // above it), and one shift hands that number back.  Ring all-reduce over a
+    // 4 x 4 torus, ns per cycle of a lone wave: 442 at two lines (655 in the
+    // shift loop), 739 at four (1193), 1309 at eight (2317).
     auto chain = [&](auto bmw_tag, auto mp_tag) {
         constexpr int BMW = decltype(bmw_tag)::value;
         constexpr bool MP = decltype(mp_tag)::value;
@@ -1169,7 +1172,7 @@ __global__ void __launch_bounds__(64 * kWaveMaxWpb) engine_wave(DevNet d) {
             unsigned long long im;
             for (;;) {
                 // -------------------------------------------------- stream offers
-                const uint32_t rem = no - nlen;  // lines left in the range (0: no stream)
+                const uint32_t rem = no - nlen;  // lines left in the range (all ones: no stream)
                 const uint32_t want = R < rend ? min(bu, rem) : 0u;
                 auto avail = [&]() -> uint32_t {
                     const uint32_t q0 = pbp - (CH ? 0u : no);

@@ -3,7 +3,9 @@ link): parity with the CPU oracle where they can go wrong -- buffers of one to
 three lines, several scenarios of a wave that idle, end and deadlock at
 different cycles, ranges of one line, two and more predecessors per range,
 more than eight, per-chunk dependencies, both arbitrations, the cycle guard at
-its last cycle -- and against the loops they replace."""
+its last cycle, stopped scenarios next to running ones -- and against the
+loops they replace; then the general round-robin loops at eight lines, which are
+compiled apart.  Which loop a load takes is checked in tests/test_host_plans.py."""
 from __future__ import annotations
 
 import numpy as np
@@ -119,15 +121,18 @@ def test_same_as_shift_loop(simmod, oracle_lib, dep, monkeypatch):
     assert got[0][4][0] == oracle_lib.simulate_workload(w, 0).processed_cycles
 
 
+EIGHT_LINES = [(4, 2, si.COLL_DBT_ALLREDUCE), (4, 4, si.COLL_RHD_ALLREDUCE), (3, 2, si.COLL_DIRECT_ALLREDUCE)]
+
+
 @pytest.mark.parametrize("dep", [si.DEP_LINE, si.DEP_CHUNK])
 @pytest.mark.parametrize("bws", [(8,), (5, 8), (1, 2, 4, 8)])
 def test_general_round_robin_eight_lines(simmod, oracle_lib, bws, dep):
     """The round-robin loops of graphs that are not lined up, at up to eight
-    lines per cycle: several feeders per link (trees), with up to four
-    predecessors per range (halving-doubling)."""
-    for coll in (si.COLL_DBT_ALLREDUCE, si.COLL_RHD_ALLREDUCE):
-        w = si.torus2d(4, 2, n_scenarios=9, seed=61, bws=bws, lat_lo=1, lat_hi=12, depths=(9, 24, 40),
-                       nbytes=128 * 16 * 7, arb=1, coll=coll)
+    lines per cycle: several feeders per link (trees), several predecessors per
+    range (halving-doubling, direct)."""
+    for X, Y, coll in EIGHT_LINES:
+        w = si.torus2d(X, Y, n_scenarios=9, seed=61, bws=bws, lat_lo=1, lat_hi=12, depths=(9, 24, 40),
+                       nbytes=128 * X * Y * 14, arb=1, coll=coll)
         w.dep = dep
         check_engine(simmod, oracle_lib, w, "wave", must_run=True)
 

@@ -267,3 +267,45 @@ def test_wave_placement_costs(plans, arb):
     assert sorted(alone + shared) == list(range(W))
     assert wave[alone].min() >= wave[shared].max() - 1e-9
     s.close()
+
+
+def test_chain_gpu_workloads(plans, monkeypatch):
+    """The loops that tests/test_gpu_chain.py means to run: the chain loops, the
+    shift loop where it is asked for, the general loops on other graphs."""
+    def loop(w, txns=None):
+        s = plans.Simulator.from_workload(w)
+        if txns is not None:
+            s.load_transactions(*txns)
+        assert launch(plans, s) == "wave"
+        s.close()
+        return "chain" if last(plans, "wv_chain") else "shift" if last(plans, "wv_lineup") else "general"
+
+    ring = []
+    for arb in (0, 1):
+        for dep in (si.DEP_LINE, si.DEP_CHUNK):
+            for coll in (si.COLL_RING_ALLREDUCE, si.COLL_RING_ALLGATHER):
+                ring.append(replace(si.torus2d(4, 4, n_scenarios=14, seed=31, bws=(1, 2, 4), depths=(1, 2, 3, 5, 16, 33),
+                                               nbytes=128 * 16 * 6, arb=arb, coll=coll), dep=dep))
+            for p, b, coll in ((3, 1, si.COLL_DIRECT_ALLREDUCE), (8, 4, si.COLL_RHD_ALLREDUCE), (7, 1, si.COLL_DBT_ALLREDUCE),
+                               (5, 2, si.COLL_RING_ALLREDUCE)):
+                ring.append(replace(si.full_mesh(p, b=b, L=6, cap=4, coll=coll, nbytes=128 * 6 * p, arb=arb), dep=dep))
+        for coll in (si.COLL_RING_ALLREDUCE,) + ((si.COLL_RHD_ALLREDUCE,) if arb == 0 else ()):  # stopped by the guard
+            w = si.torus2d(4, 2, n_scenarios=12, seed=51, bws=(2,), depths=(2, 5, 16), nbytes=128 * 8 * 24, arb=arb, coll=coll)
+            ring.append(replace(w, order=si.gray_torus_order(4, 2)) if coll == si.COLL_RHD_ALLREDUCE else w)
+    assert {loop(w) for w in ring} == {"chain"}
+    src, dst = np.arange(5, dtype=np.int32), (np.arange(5, dtype=np.int32) + 1) % 5
+    assert loop(si.full_mesh(5, b=2, L=3, cap=3, nbytes=128 * 5),
+                (src, dst, np.zeros(6, np.int64), np.zeros(0, np.int64))) == "chain"
+    same = si.torus2d(4, 4, n_scenarios=40, seed=8, bws=(1, 2, 4), depths=(4, 16, 40), nbytes=128 * 16 * 40)
+    for env, want in (("", "chain"), ("shift", "shift"), ("general", "general")):
+        monkeypatch.setenv("SIMGPU_WAVE_LOOP", env)
+        assert loop(same) == want
+    monkeypatch.delenv("SIMGPU_WAVE_LOOP")
+    from tests.test_gpu_chain import EIGHT_LINES
+    for X, Y, coll in EIGHT_LINES:
+        assert loop(si.torus2d(X, Y, n_scenarios=9, seed=61, bws=(5, 8), depths=(9, 24, 40), nbytes=128 * X * Y * 14, arb=1,
+                               coll=coll)) == "general"
+    rp, ci, three = np.array([0, 1, 2, 3], np.int32), np.array([1, 2, 0], np.int32), np.full(3, 8, np.int32)
+    w = si.Workload("ring3", 3, 3, rp, ci, 1, three, three, three, 1, -1, 0)
+    assert loop(w, (np.array([0, 1, 2], np.int32), np.array([2, 0, 1], np.int32), np.zeros(4, np.int64),
+                    np.zeros(0, np.int64))) == "general"
